@@ -8,6 +8,7 @@
 // thread-per-output kernels these replace needed two loads per multiply-add and ran at 1.5 TFLOP/s.
 #include "common.h"
 #include "conv_internal.h"
+#include "index_math.h"
 #include "quad_io.h"
 
 namespace k3 {
@@ -132,9 +133,10 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
             }
         }
     };
-    // Weights of step s: the lane (row ln, slot kg) takes the four channels of its slot.  Rows,
-    // channels and taps beyond the layer's lie outside the descriptor's range and read as zero
-    // (without a descriptor: they are read from a clamped place and replaced).
+    // Weights of step s: the lane (row ln, slot kg) takes the four channels of its slot.  Rows and
+    // channels beyond the layer's get a lane offset outside the descriptor's range and read as zero, as
+    // do taps where a lane's offset holds the tap; where the tap is in the scalar offset it is clamped
+    // (without a descriptor: all are read from a clamped place and replaced).
     const __amdgpu_buffer_rsrc_t wrsrc = rsrc_of(p.w, BUF ? 27 * K * M * (int)sizeof(T) : 0);
     int lo[MB][4];               // element offset inside a tap, per chunk
     bool keep[MB][4];
@@ -151,13 +153,13 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
         }
     };
     auto weights = [&](int s, float (&a)[MB][4]) __attribute__((always_inline)) {
-        const int tap = S == 4 ? s : (4 * s + kg) / S;
+        const int tap = general_tap(S, s, kg);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             if constexpr (BUF) {
                 // a step that is one tap has a wave-uniform offset, else the lane's own is added
                 const int toff = (BWD ? 26 - tap : tap) * K * M;
-                const int soff = S == 4 ? toff * (int)sizeof(T) : 0;
+                const int soff = general_weight_soff<int>(S, s, BWD, K, M, (int)sizeof(T));
                 auto at = [&](int o) __attribute__((always_inline)) { return S == 4 ? o : o < 0 || tap > 26 ? -1 : o + toff; };
                 if constexpr (BWD) {   // the contraction runs along the fastest axis: one load
                     const f32x4 v = buf<T>::quad(wrsrc, at(lo[mb][0]), soff);

@@ -1,0 +1,26 @@
+// Index arithmetic of the kernels in a form that a host compiler can check too: no HIP types.
+#pragma once
+#include <stdint.h>
+#ifdef __HIPCC__
+#define K3_HD __host__ __device__ __forceinline__
+#else
+#define K3_HD inline
+#endif
+
+namespace k3 {
+
+// General 3x3x3 kernel: the tap a lane group's slot of step s belongs to (S slots per voxel and chunk;
+// the last step may hold slots that belong to none, and a wave may look ahead past the last step).
+K3_HD int general_tap(int S, int s, int kg) { return S == 4 ? s : (4 * s + kg) / S; }
+
+// Byte offset a wave adds to a step's weight loads, the same for all its lanes (S = 4: a step is one tap).
+// A wave that looks ahead past the last tap reads the last one again: a scalar offset is no part of
+// a descriptor's range check, so it has to lie inside the tensor by itself.
+template <typename I>
+K3_HD I general_weight_soff(int S, int s, bool bwd, I K, I M, int size)
+{
+    const int tap = general_tap(S, s, 0) < 26 ? general_tap(S, s, 0) : 26;
+    return S == 4 ? (bwd ? 26 - tap : tap) * K * M * size : 0;
+}
+
+}  // namespace k3

@@ -1,0 +1,46 @@
+"""The kernels' index arithmetic (csrc/index_math.h), compiled for the host: every offset a kernel can
+form lies inside its tensor, also where 32 bits would not hold it."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = r"""
+#include "index_math.h"
+using namespace k3;
+extern "C" {
+int64_t weight_soff(int S, int s, int bwd, int64_t K, int64_t M, int size) { return general_weight_soff<int64_t>(S, s, bwd, K, M, size); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("index_math")
+    cpp, so = str(d / "index_math.cpp"), str(d / "index_math.so")
+    with open(cpp, "w") as f:
+        f.write(SRC)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-fsanitize=undefined", "-fno-sanitize-recover", "-static-libubsan",
+                           "-I" + os.path.join(ROOT, "paper_1811_12174_amd", "csrc"), "-o", so, cpp])
+    L = ctypes.CDLL(so)
+    q, i = ctypes.c_int64, ctypes.c_int
+    L.weight_soff.restype, L.weight_soff.argtypes = q, [i, i, i, q, q, i]
+    return L
+
+
+@pytest.mark.parametrize("S", [1, 2, 4])
+@pytest.mark.parametrize("wk", [1, 4])       # waves that split the steps
+@pytest.mark.parametrize("bwd", [0, 1])
+def test_general_kernel_asks_for_no_weights_outside_the_tensor(lib, S, wk, bwd):
+    K, M, size = 40, 24, 4
+    nstep, ahead = (27 * S + 3) // 4, 2
+    mysteps = (nstep + wk - 1) // wk
+    for w in range(wk):
+        for i in range(mysteps + ahead):
+            if i >= ahead and i >= mysteps:      # the kernel looks ahead only while its own steps last
+                continue
+            off = lib.weight_soff(S, i * wk + w, bwd, K, M, size)
+            # the lanes add up to one tap's K x M
+            assert 0 <= off and off + K * M * size <= 27 * K * M * size, (S, wk, w, i)
