@@ -11,7 +11,12 @@
 #include "index_math.h"
 #include "quad_io.h"
 
+#include <type_traits>
+
 namespace k3 {
+
+// voxel offsets inside a tile: with descriptors its span is below 2 GiB, without them it may be anything
+template <bool BUF> using TileOff = std::conditional_t<BUF, int, int64_t>;
 
 template <typename T>
 struct GenConv {
@@ -103,13 +108,13 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
 
     // the lane's halo items: (voxel, quad) i = tid + 256 k; offset of the voxel from the halo tile's
     // first one, negative outside the volume
-    int vo[ITEMS];
+    TileOff<BUF> vo[ITEMS];
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int vox = (tid + k * 256) / S;
         const int lw = vox % HW, lh = (vox / HW) % HH, ld = vox / (HW * HH);
         const unsigned gd = d0 + ld - 1, gh = h0 + lh - 1, gw = w0 + lw - 1;
-        vo[k] = vox < NHALO && gd < (unsigned)p.D && gh < (unsigned)p.H && gw < (unsigned)p.W ? (ld * p.H + lh) * p.W + lw : -1;
+        vo[k] = vox < NHALO && gd < (unsigned)p.D && gh < (unsigned)p.H && gw < (unsigned)p.W ? tile_offset<TileOff<BUF>>(ld, lh, lw, p.H, p.W) : -1;
     }
     const int64_t halo0 = (((int64_t)n * p.D + d0 - 1) * p.H + h0 - 1) * p.W + w0 - 1;
     const QuadSrc xsrc = {rsrc_of(p.src1 + halo0 * p.c1, 0x7ffffff0), rsrc_of((p.src2 ? p.src2 : p.src1) + halo0 * p.c2, 0x7ffffff0)};
@@ -378,16 +383,16 @@ __global__ __launch_bounds__(256, 3) void conv_general_wgrad_kernel(GenWgrad<T> 
     const int cin = p.c1 + p.c2;
     const int ci0 = ((int)blockIdx.y / p.ncb) * 16, co0 = ((int)blockIdx.y % p.ncb) * 16;
     // offset of the lane's voxel in each item (tid + 256 k: voxel and quad) from the tile's first one
-    int hx[XI], hg[GI];
+    TileOff<BUF> hx[XI], hg[GI];
 #pragma unroll
     for (int k = 0; k < XI; ++k) {
         const int vox = (tid + k * 256) >> 2;
-        hx[k] = ((vox / (HW * HH)) * p.H + (vox / HW) % HH) * p.W + vox % HW;
+        hx[k] = tile_offset<TileOff<BUF>>(vox / (HW * HH), (vox / HW) % HH, vox % HW, p.H, p.W);
     }
 #pragma unroll
     for (int k = 0; k < GI; ++k) {
         const int vox = (tid + k * 256) >> 2;
-        hg[k] = ((vox / (TW * TH)) * p.H + (vox / TW) % TH) * p.W + vox % TW;
+        hg[k] = tile_offset<TileOff<BUF>>(vox / (TW * TH), (vox / TW) % TH, vox % TW, p.H, p.W);
     }
     f32x4 sx[XI], sg[GI];
     auto fetch = [&](int tile) __attribute__((always_inline)) {

@@ -23,4 +23,9 @@ K3_HD I general_weight_soff(int S, int s, bool bwd, I K, I M, int size)
     return S == 4 ? (bwd ? 26 - tap : tap) * K * M * size : 0;
 }
 
+// Offset of voxel (d, h, w) of a tile from the tile's first voxel.  I: 32 bits where a tile's span is
+// known to be small, else 64.
+template <typename I>
+K3_HD I tile_offset(int d, int h, int w, int H, int W) { return ((I)d * H + h) * W + w; }
+
 }  // namespace k3

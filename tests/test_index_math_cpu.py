@@ -12,6 +12,8 @@ SRC = r"""
 using namespace k3;
 extern "C" {
 int64_t weight_soff(int S, int s, int bwd, int64_t K, int64_t M, int size) { return general_weight_soff<int64_t>(S, s, bwd, K, M, size); }
+int64_t offset64(int d, int h, int w, int H, int W) { return tile_offset<int64_t>(d, h, w, H, W); }
+int64_t offset32(int d, int h, int w, int H, int W) { return tile_offset<int>(d, h, w, H, W); }
 }
 """
 
@@ -27,6 +29,8 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(so)
     q, i = ctypes.c_int64, ctypes.c_int
     L.weight_soff.restype, L.weight_soff.argtypes = q, [i, i, i, q, q, i]
+    for f in (L.offset32, L.offset64):
+        f.restype, f.argtypes = q, [i, i, i, i, i]
     return L
 
 
@@ -44,3 +48,14 @@ def test_general_kernel_asks_for_no_weights_outside_the_tensor(lib, S, wk, bwd):
             off = lib.weight_soff(S, i * wk + w, bwd, K, M, size)
             # the lanes add up to one tap's K x M
             assert 0 <= off and off + K * M * size <= 27 * K * M * size, (S, wk, w, i)
+
+
+def test_offsets_inside_a_tile_of_wide_planes(lib):
+    # without descriptors: five planes of 21000 x 21000 voxels pass 2^31
+    for H, W in ((3, 5), (21000, 21000), (2 ** 31 - 1, 7), (1, 2 ** 31 - 1)):
+        for d, h, w in ((0, 0, 0), (5, 5, 9), (5, 0, 0), (1, 3, 2)):
+            assert lib.offset64(d, h, w, H, W) == (d * H + h) * W + w
+    # with them a tile spans less than 2 GiB: 6 (H + 1) W elements of 4 bytes
+    H, W = 9000, 9000
+    assert 6 * (H + 1) * W * 4 < 2 ** 31
+    assert lib.offset32(5, 5, 9, H, W) == (5 * H + 5) * W + 9
