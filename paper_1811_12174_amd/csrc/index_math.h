@@ -28,4 +28,7 @@ K3_HD I general_weight_soff(int S, int s, bool bwd, I K, I M, int size)
 template <typename I>
 K3_HD I tile_offset(int d, int h, int w, int H, int W) { return ((I)d * H + h) * W + w; }
 
+// 16-byte lane fragments of one packed form of a weight tensor.
+K3_HD int64_t pack_fragments(int taps, int cin, int cout) { return (int64_t)taps * cin * cout / 8; }
+
 }  // namespace k3

@@ -9,6 +9,7 @@
 #include "common.h"
 #include "conv_internal.h"
 #include "conv_mfma.h"
+#include "index_math.h"
 
 namespace k3 {
 
@@ -23,7 +24,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(PackList p)
     int k = 0;
     while (k + 1 < p.n && blockIdx.x >= p.first[k + 1]) ++k;
     const PackJob q = p.job[k];
-    const unsigned per = (unsigned)(q.taps * q.cin * q.cout / 8);    // lane fragments of one form
+    const unsigned per = (unsigned)pack_fragments(q.taps, q.cin, q.cout);    // lane fragments of one form: both fit 31 bits
     unsigned r = (blockIdx.x - p.first[k]) * 256 + threadIdx.x;
     if (r >= 2 * per) return;
     const bool bwd = r >= per;
@@ -65,7 +66,7 @@ int launch_pack(const PackJob *jobs, int n, hipStream_t st)
         for (int k = 0; k < p.n; ++k) {
             p.job[k] = jobs[at + k];
             p.first[k] = (unsigned)blocks;
-            const int64_t frags = (int64_t)2 * p.job[k].taps * p.job[k].cin * p.job[k].cout / 8;
+            const int64_t frags = 2 * pack_fragments(p.job[k].taps, p.job[k].cin, p.job[k].cout);
             if (frags > 0x7fffffffLL) return K3_E_UNSUPPORTED;
             blocks += (frags + 255) / 256;
         }

@@ -12,6 +12,7 @@ SRC = r"""
 using namespace k3;
 extern "C" {
 int64_t weight_soff(int S, int s, int bwd, int64_t K, int64_t M, int size) { return general_weight_soff<int64_t>(S, s, bwd, K, M, size); }
+int64_t fragments(int taps, int cin, int cout) { return pack_fragments(taps, cin, cout); }
 int64_t offset64(int d, int h, int w, int H, int W) { return tile_offset<int64_t>(d, h, w, H, W); }
 int64_t offset32(int d, int h, int w, int H, int W) { return tile_offset<int>(d, h, w, H, W); }
 }
@@ -29,6 +30,7 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(so)
     q, i = ctypes.c_int64, ctypes.c_int
     L.weight_soff.restype, L.weight_soff.argtypes = q, [i, i, i, q, q, i]
+    L.fragments.restype, L.fragments.argtypes = q, [i, i, i]
     for f in (L.offset32, L.offset64):
         f.restype, f.argtypes = q, [i, i, i, i, i]
     return L
@@ -59,3 +61,9 @@ def test_offsets_inside_a_tile_of_wide_planes(lib):
     H, W = 9000, 9000
     assert 6 * (H + 1) * W * 4 < 2 ** 31
     assert lib.offset32(5, 5, 9, H, W) == (5 * H + 5) * W + 9
+
+
+@pytest.mark.parametrize("taps,cin,cout", [(27, 32, 64), (27, 8928, 8928), (27, 17824, 17824), (8, 16416, 16416), (8, 32768, 32768)])
+def test_fragments_of_large_weight_tensors(lib, taps, cin, cout):
+    # the launch refuses 2^31 fragments of the two forms; 2^31 weights (a quarter as many fragments) it takes
+    assert lib.fragments(taps, cin, cout) == taps * cin * cout // 8
