@@ -18,6 +18,7 @@
 #include "common.h"
 #include "conv_internal.h"
 #include "conv_mfma.h"
+#include "index_math.h"
 
 namespace k3 {
 
@@ -1468,7 +1469,7 @@ static int mfma_variant(const MfmaParams &p, int64_t mblocks)
     // 22 us against 27 on the pipelined kernel, 4^3 128->128: 8.5 against 13.7 -- 59.8 on the first one;
     // 32^3 64->64, 1024: 18 against 11)
     const int64_t cubes = (int64_t)p.N * ((p.D + 3) / 4) * ((p.H + 3) / 4) * ((p.W + 3) / 4);
-    if (fits && cubes * mblocks <= 512) return 5;
+    if (fits && cubes * mblocks <= 512 && small_weights_fit(p.c1 + p.c2)) return 5;
     if (!p.mask && fits) {
         const int64_t big = (int64_t)p.N * ((p.D + 7) / 8) * ((p.H + 7) / 8) * ((p.W + 15) / 16);
         const int64_t small = (int64_t)p.N * ((p.D + 3) / 4) * ((p.H + 7) / 8) * ((p.W + 7) / 8);

@@ -11,6 +11,7 @@
 #include "common.h"
 #include "conv_internal.h"
 #include "conv_mfma.h"
+#include "index_math.h"
 
 namespace k3 {
 
@@ -44,14 +45,15 @@ __global__ __launch_bounds__(256, MB == 1 ? 3 : 2) void conv_small_kernel(MfmaPa
     const int n = (int)(t / p.ntd);
 
     // weights of (tap j of the wave, chunk c): row ln of the block <-> packed row, slot kg <-> (half chunk, lane half)
-    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(p.packed), 0, 0x7ffffff0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t *>(p.packed) + packed_block(m0 >> 5, nkc) / 2, 0, 0x7ffffff0, 0x00020000);   // (the blocks of a workgroup lie in one)
     const unsigned wlane = (unsigned)((kg >> 1) * 1024 + ((kg & 1) * 32 + (ln >> 2) * 8 + (ln & 3)) * 16);
     auto weights = [&](int c, int j, bf16x8 (&a)[MB]) __attribute__((always_inline)) {
         const bool there = 2 * c + (kg >> 1) < nkc;     // an odd number of 16-channel steps ends in half a chunk
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
             const int m = m0 + mb * 16;
-            const unsigned soff = (unsigned)((((m >> 5) * 27 + wv + 4 * j) * nkc + 2 * c) * 1024 + ((m >> 4) & 1) * 64);
+            const unsigned soff = packed_step(wv + 4 * j, nkc, 2 * c) + ((m >> 4) & 1) * 64;
             a[mb] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, there && m < M ? wlane : 0xffffffffu, soff, 0));
         }
     };

@@ -31,4 +31,10 @@ K3_HD I tile_offset(int d, int h, int w, int H, int W) { return ((I)d * H + h) *
 // 16-byte lane fragments of one packed form of a weight tensor.
 K3_HD int64_t pack_fragments(int taps, int cin, int cout) { return (int64_t)taps * cin * cout / 8; }
 
+// Packed 3x3x3 weights, [32-channel block][27][nkc][1 KB]: bytes to a block of output channels, and from
+// there to (tap, 16-channel step).  A block alone stays below 2 GiB where small_weights_fit says so.
+K3_HD int64_t packed_block(int block, int nkc) { return (int64_t)block * 27 * nkc * 1024; }
+K3_HD unsigned packed_step(int tap, int nkc, int kc) { return (unsigned)((tap * nkc + kc) * 1024); }
+K3_HD bool small_weights_fit(int64_t K) { return 27 * (K / 16) * 1024 < 0x7ffffff0LL; }
+
 }  // namespace k3

@@ -12,6 +12,9 @@ SRC = r"""
 using namespace k3;
 extern "C" {
 int64_t weight_soff(int S, int s, int bwd, int64_t K, int64_t M, int size) { return general_weight_soff<int64_t>(S, s, bwd, K, M, size); }
+int64_t block(int b, int nkc) { return packed_block(b, nkc); }
+int64_t step(int tap, int nkc, int kc) { return packed_step(tap, nkc, kc); }
+int fit(int64_t K) { return small_weights_fit(K); }
 int64_t fragments(int taps, int cin, int cout) { return pack_fragments(taps, cin, cout); }
 int64_t offset64(int d, int h, int w, int H, int W) { return tile_offset<int64_t>(d, h, w, H, W); }
 int64_t offset32(int d, int h, int w, int H, int W) { return tile_offset<int>(d, h, w, H, W); }
@@ -30,6 +33,9 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(so)
     q, i = ctypes.c_int64, ctypes.c_int
     L.weight_soff.restype, L.weight_soff.argtypes = q, [i, i, i, q, q, i]
+    L.block.restype, L.block.argtypes = q, [i, i]
+    L.step.restype, L.step.argtypes = q, [i, i, i]
+    L.fit.restype, L.fit.argtypes = i, [q]
     L.fragments.restype, L.fragments.argtypes = q, [i, i, i]
     for f in (L.offset32, L.offset64):
         f.restype, f.argtypes = q, [i, i, i, i, i]
@@ -67,3 +73,16 @@ def test_offsets_inside_a_tile_of_wide_planes(lib):
 def test_fragments_of_large_weight_tensors(lib, taps, cin, cout):
     # the launch refuses 2^31 fragments of the two forms; 2^31 weights (a quarter as many fragments) it takes
     assert lib.fragments(taps, cin, cout) == taps * cin * cout // 8
+
+
+@pytest.mark.parametrize("K", [16, 256, 38912, 1 << 20, 1242736])
+def test_packed_weights_of_the_small_volume_kernel(lib, K):
+    # 1024 output channels: 32 blocks, whose packed form passes 2 GiB from 38912 input channels on
+    assert lib.fit(K)
+    nkc = K // 16
+    for b in (0, 1, 31):
+        for tap in (0, 13, 26):
+            for kc in (0, nkc - 1):
+                assert 0 <= lib.step(tap, nkc, kc) < 2 ** 31 - 1024
+                assert lib.block(b, nkc) + lib.step(tap, nkc, kc) == ((b * 27 + tap) * nkc + kc) * 1024
+    assert not lib.fit(1242784)
