@@ -31,6 +31,7 @@ struct GenConv {
     int N, D, H, W;
     int ntd, nth, ntw, ncb;            // tiles per axis, output-channel groups
     int64_t total, per_xcd;
+    bool vout;                         // outputs (and omask) are accessed as quads
 };
 
 // Four consecutive channels ch .. ch+3 of voxel v of the concatenation [p1 | p2]; zero beyond it.
@@ -76,8 +77,8 @@ __device__ __forceinline__ f32x4 load_quad_buf(const QuadSrc &s, int c1, int c2,
 // their sums through LDS in a fixed order.
 // One output block takes 128 registers, so that four workgroups share a CU: 16 -> 16 channels at 48^3
 // (864 workgroups, of which 768 fitted before and the rest ran alone) 27.2 -> 24.5 us.
-// BUF: tensors and weights are read through buffer descriptors (channel counts in whole quads, a
-// tile's span below 2 GiB); else element by element.
+// BUF: tensors and weights are read through buffer descriptors (channel counts in whole quads on quad
+// boundaries, a tile's span below 2 GiB); else element by element.
 template <typename T, int TD, int TH, int TW, int WN, int S, int MB, bool BWD, bool BUF>
 __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_kernel(GenConv<T> p)
 {
@@ -235,7 +236,6 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
     }
 
     // a lane holds output channels m .. m+3 of one voxel of a block
-    const bool vout = p.cd1 % 4 == 0 && p.cd2 % 4 == 0;
     auto emit = [&](int blk, int mb, f32x4 v) __attribute__((always_inline)) {
         const int i = blk * 16 + ln;
         const int gd = d0 + i / (TW * TH), gh = h0 + (i / TW) % TH, gw = w0 + i % TW;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
             float x = v[r] + (p.bias && m + r < M ? p.bias[m + r] : 0.f);
             v[r] = (p.relu && !(x > 0.f)) ? 0.f : x;
         }
-        if (vout) {
+        if (p.vout) {
             const bool d1 = m < p.cd1;
             const int64_t o = d1 ? vox * p.cd1 + m : vox * p.cd2 + (m - p.cd1);
             if (d1 && p.omask) v = keep_positive(v, buf<T>::ld4(p.omask + o));
@@ -302,14 +302,19 @@ static int launch_general(GenConv<T> p, hipStream_t st)
     return K3_OK;
 }
 
+static uintptr_t bits(const void *p) { return (uintptr_t)p; }
+
 // 128-voxel tiles with two output blocks per workgroup where that gives every CU one, else with
 // one, else 32-voxel tiles (16 -> 16 channels at 12^3: 27 workgroups of the large kind)
 template <typename T, int S, bool BWD>
-static int launch_general_size(const GenConv<T> &p, hipStream_t st)
+static int launch_general_size(GenConv<T> p, hipStream_t st)
 {
     const int64_t M = p.cd1 + p.cd2, K = p.c1 + p.c2, C = K > M ? K : M;
     const int64_t big = (int64_t)p.N * ((p.D + 3) / 4) * ((p.H + 3) / 4) * ((p.W + 7) / 8);
-    const bool buf = p.c1 % 4 == 0 && p.c2 % 4 == 0 && 6 * (int64_t)(p.H + 1) * p.W * C * 4 < 0x7fffffffLL && 27 * K * M * 4 < 0x7fffffffLL;
+    // (of the weights only backward-data reads quads)
+    const bool buf = whole_quads(p.c1 | p.c2, bits(p.src1) | bits(p.src2) | bits(p.mask) | (BWD ? bits(p.w) : 0), sizeof(T)) &&
+                     6 * (int64_t)(p.H + 1) * p.W * C * 4 < 0x7fffffffLL && 27 * K * M * 4 < 0x7fffffffLL;
+    p.vout = whole_quads(p.cd1 | p.cd2, bits(p.dst1) | bits(p.dst2) | bits(p.omask), sizeof(T));
     if (!buf) return launch_general<T, 4, 4, 8, 4, S, 1, BWD, false>(p, st);
     if (M > 16 && big * ((M + 31) / 32) >= 256) return launch_general<T, 4, 4, 8, 4, S, 2, BWD, true>(p, st);
     if (big * ((M + 15) / 16) >= 256) return launch_general<T, 4, 4, 8, 4, S, 1, BWD, true>(p, st);
@@ -548,7 +553,7 @@ static int wgrad_general_t(const ConvArgs &a, float *dW, float *db, float *ws, h
     p.per_split = 27 * cin * a.cout + a.cout;
     const dim3 grid((unsigned)q.nsplit, (unsigned)blocks);
     const int64_t span = 6 * (int64_t)(p.H + 1) * p.W * (cin > a.cout ? cin : a.cout) * 4;
-    const bool buf = p.c1 % 4 == 0 && p.c2 % 4 == 0 && p.cout % 4 == 0 && span < 0x7fffffffLL;
+    const bool buf = whole_quads(p.c1 | p.c2 | p.cout, bits(p.x1) | bits(p.x2) | bits(p.g) | bits(p.mask), sizeof(T)) && span < 0x7fffffffLL;
     if (q.small && buf) conv_general_wgrad_kernel<T, 2, 4, 8, true><<<grid, 256, 0, st>>>(p);
     else if (q.small) conv_general_wgrad_kernel<T, 2, 4, 8, false><<<grid, 256, 0, st>>>(p);
     else if (buf) conv_general_wgrad_kernel<T, 4, 4, 8, true><<<grid, 256, 0, st>>>(p);

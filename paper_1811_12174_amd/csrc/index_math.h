@@ -37,4 +37,11 @@ K3_HD int64_t packed_block(int block, int nkc) { return (int64_t)block * 27 * nk
 K3_HD unsigned packed_step(int tap, int nkc, int kc) { return (unsigned)((tap * nkc + kc) * 1024); }
 K3_HD bool small_weights_fit(int64_t K) { return 27 * (K / 16) * 1024 < 0x7ffffff0LL; }
 
+// Whether four channels at a time are one aligned access: the channel counts and the base addresses
+// (each or-ed together; null addresses do not count), and the bytes of an element.
+K3_HD bool whole_quads(int64_t channels, uintptr_t at, int size)
+{
+    return channels % 4 == 0 && (at & (uintptr_t)(4 * size - 1)) == 0;
+}
+
 }  // namespace k3

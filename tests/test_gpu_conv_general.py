@@ -67,3 +67,52 @@ def test_general_kernels(orc, case, masked):
     rW, rb = orc.conv3d_bwd_weight(x64, g64)
     assert rel_l2(to_f64(dW), rW) < 1e-5
     assert rel_l2(to_f64(db), rb) < 1e-5
+
+
+# channel counts in whole quads on tensors one element past a quad's boundary: each of them alone and all
+# (N, D, H, W), c1, c2, cout, dtype; the second size takes 128-voxel tiles
+SHIFTED = [((1, 5, 6, 9), 8, 0, 12, "f32"), ((1, 5, 6, 9), 8, 8, 20, "bf16"), ((1, 28, 29, 33), 16, 0, 16, "f32"), ((1, 6, 7, 9), 16, 16, 32, "bf16")]
+
+
+@pytest.mark.parametrize("case", SHIFTED, ids=lambda c: "x".join(map(str, c[0] + c[1:])))
+@pytest.mark.parametrize("which", ["x", "w", "dy", "masks", "out", "all"])
+def test_tensors_off_the_quad_boundary(orc, case, which):
+    import torch
+    from paper_1811_12174_amd import k3
+    from gpu_util import to_dev, to_f64, empty, rel_l2
+    sp, c1, c2, co, dt = case
+    tol = 1e-5 if dt == "f32" else 4e-3      # as above
+
+    def put(t, kind):
+        if which not in (kind, "all"):
+            return t
+        flat = torch.empty(t.numel() + 1, device=t.device, dtype=t.dtype)
+        flat[1:].copy_(t.reshape(-1))
+        return flat[1:].view(t.shape)
+
+    def new(c):
+        return put(empty(sp + (c,), dt).fill_(float("nan")), "out")
+    x, w, dy = synth.activations(620, sp + (c1 + c2,), dt), synth.conv_weights(621, c1 + c2, co, dt), synth.activations(622, sp + (co,), dt)
+    ym, om = synth.activations(623, sp + (co,), dt), synth.activations(624, sp + (c1,), dt)
+    xd = to_dev(x, dt)
+    x1, x2 = put(xd[..., :c1].contiguous(), "x"), put(xd[..., c1:].contiguous(), "x") if c2 else None
+    wd, dyd, ymd, omd = put(to_dev(w, dt), "w"), put(to_dev(dy, dt), "dy"), put(to_dev(ym, dt), "masks"), put(to_dev(om, dt), "masks")
+
+    y, dx, dx2 = new(co), new(c1), new(c2) if c2 else None
+    k3.conv3d_fwd(x1, wd, None, None, 1, y, x2=x2)
+    k3.conv3d_bwd_data(dyd, ymd, wd, None, dx, dx2=dx2, dx_mask=omd)
+    dW, db = torch.full((3, 3, 3, c1 + c2, co), float("nan"), device="cuda"), torch.full((co,), float("nan"), device="cuda")
+    ws = torch.empty(k3.conv3d_bwd_weight_workspace_bytes(x1, dyd, x2=x2), device="cuda", dtype=torch.uint8)
+    k3.conv3d_bwd_weight(x1, dyd, ymd, dW, db, ws, x2=x2)
+    torch.cuda.synchronize()
+
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    g64 = orc.relu_bwd(dy.astype(np.float64), ym.astype(np.float64))
+    assert rel_l2(to_f64(y), orc.conv3d_fwd(x64, w64, np.zeros(co), relu=True)) < tol
+    rdx = orc.conv3d_bwd_data(g64, w64)
+    assert rel_l2(to_f64(dx), orc.relu_bwd(rdx[..., :c1].copy(), om.astype(np.float64))) < tol
+    if c2:
+        assert rel_l2(to_f64(dx2), rdx[..., c1:]) < tol
+    rW, rb = orc.conv3d_bwd_weight(x64, g64)
+    assert rel_l2(to_f64(dW), rW) < 1e-5
+    assert rel_l2(to_f64(db), rb) < 1e-5

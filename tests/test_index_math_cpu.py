@@ -15,6 +15,7 @@ int64_t weight_soff(int S, int s, int bwd, int64_t K, int64_t M, int size) { ret
 int64_t block(int b, int nkc) { return packed_block(b, nkc); }
 int64_t step(int tap, int nkc, int kc) { return packed_step(tap, nkc, kc); }
 int fit(int64_t K) { return small_weights_fit(K); }
+int quads(int64_t channels, uint64_t at, int size) { return whole_quads(channels, at, size); }
 int64_t fragments(int taps, int cin, int cout) { return pack_fragments(taps, cin, cout); }
 int64_t offset64(int d, int h, int w, int H, int W) { return tile_offset<int64_t>(d, h, w, H, W); }
 int64_t offset32(int d, int h, int w, int H, int W) { return tile_offset<int>(d, h, w, H, W); }
@@ -36,6 +37,7 @@ def lib(tmp_path_factory):
     L.block.restype, L.block.argtypes = q, [i, i]
     L.step.restype, L.step.argtypes = q, [i, i, i]
     L.fit.restype, L.fit.argtypes = i, [q]
+    L.quads.restype, L.quads.argtypes = i, [q, ctypes.c_uint64, i]
     L.fragments.restype, L.fragments.argtypes = q, [i, i, i]
     for f in (L.offset32, L.offset64):
         f.restype, f.argtypes = q, [i, i, i, i, i]
@@ -86,3 +88,13 @@ def test_packed_weights_of_the_small_volume_kernel(lib, K):
                 assert 0 <= lib.step(tap, nkc, kc) < 2 ** 31 - 1024
                 assert lib.block(b, nkc) + lib.step(tap, nkc, kc) == ((b * 27 + tap) * nkc + kc) * 1024
     assert not lib.fit(1242784)
+
+
+@pytest.mark.parametrize("size", [2, 4])
+def test_quads_lie_on_their_own_boundary(lib, size):
+    a, b = 0x7F0000001000, 0x7F0000A00200
+    assert lib.quads(8 | 16 | 0, a | b | 0, size)
+    for shift in (1, 2, 3):
+        assert not lib.quads(8 | 16, a | (b + shift * size), size)
+        assert not lib.quads(8 | (16 + shift), a | b, size)
+    assert lib.quads(8, (a + 4 * size) | b, size)
