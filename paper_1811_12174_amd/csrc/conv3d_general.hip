@@ -386,7 +386,8 @@ __global__ __launch_bounds__(256, 3) void conv_general_wgrad_kernel(GenWgrad<T> 
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = lane >> 4, ln = lane & 15;
     const int cin = p.c1 + p.c2;
-    const int ci0 = ((int)blockIdx.y / p.ncb) * 16, co0 = ((int)blockIdx.y % p.ncb) * 16;
+    const int split = (int)(blockIdx.x % (unsigned)p.nsplit), blk = (int)(blockIdx.x / (unsigned)p.nsplit);
+    const int ci0 = (blk / p.ncb) * 16, co0 = (blk % p.ncb) * 16;
     // offset of the lane's voxel in each item (tid + 256 k: voxel and quad) from the tile's first one
     TileOff<BUF> hx[XI], hg[GI];
 #pragma unroll
@@ -449,7 +450,7 @@ __global__ __launch_bounds__(256, 3) void conv_general_wgrad_kernel(GenWgrad<T> 
 #pragma unroll
     for (int j = 0; j < 7; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    int tile = blockIdx.x;
+    int tile = split;
     fetch(tile);
     while (true) {
 #pragma unroll
@@ -481,7 +482,7 @@ __global__ __launch_bounds__(256, 3) void conv_general_wgrad_kernel(GenWgrad<T> 
         if (tile >= p.tiles) break;
         __syncthreads();
     }
-    float *out = p.ws + (int64_t)blockIdx.x * p.per_split;
+    float *out = p.ws + (int64_t)split * p.per_split;
     const int co = co0 + ln;
     if (co >= p.cout) return;
 #pragma unroll
@@ -536,7 +537,7 @@ static int wgrad_general_t(const ConvArgs &a, float *dW, float *db, float *ws, h
     const int64_t cin = a.c1 + a.c2;
     const GenWgradPlan q = general_wgrad_plan(a.N, a.D, a.H, a.W, cin, a.cout);
     const int64_t blocks = ((cin + 15) / 16) * ((a.cout + 15) / 16);
-    if (blocks > 65535 || q.tiles > 0x7fffffffLL) return K3_E_UNSUPPORTED;
+    if (q.nsplit * blocks > 0x7fffffffLL || q.tiles > 0x7fffffffLL) return K3_E_UNSUPPORTED;
     GenWgrad<T> p{};
     p.x1 = (const T *)a.x; p.x2 = (const T *)a.x2;
     p.c1 = (int)a.c1; p.c2 = (int)a.c2;
@@ -551,7 +552,7 @@ static int wgrad_general_t(const ConvArgs &a, float *dW, float *db, float *ws, h
     p.nsplit = (int)q.nsplit;
     p.ncb = (int)((a.cout + 15) / 16);
     p.per_split = 27 * cin * a.cout + a.cout;
-    const dim3 grid((unsigned)q.nsplit, (unsigned)blocks);
+    const dim3 grid((unsigned)(q.nsplit * blocks));
     const int64_t span = 6 * (int64_t)(p.H + 1) * p.W * (cin > a.cout ? cin : a.cout) * 4;
     const bool buf = whole_quads(p.c1 | p.c2 | p.cout, bits(p.x1) | bits(p.x2) | bits(p.g) | bits(p.mask), sizeof(T)) && span < 0x7fffffffLL;
     if (q.small && buf) conv_general_wgrad_kernel<T, 2, 4, 8, true><<<grid, 256, 0, st>>>(p);

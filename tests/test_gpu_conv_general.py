@@ -116,3 +116,19 @@ def test_tensors_off_the_quad_boundary(orc, case, which):
     rW, rb = orc.conv3d_bwd_weight(x64, g64)
     assert rel_l2(to_f64(dW), rW) < 1e-5
     assert rel_l2(to_f64(db), rb) < 1e-5
+
+
+def test_weight_gradient_of_more_blocks_than_a_grid_axis_has():
+    # 65537 blocks of 16 x 16 channels; two voxels along w, so three taps meet a voxel: dW = x g by hand
+    import torch
+    from paper_1811_12174_amd import k3
+    co = 16 * 65536 + 3
+    g = torch.arange(2 * co, device="cuda", dtype=torch.float32).remainder_(251.0).view(1, 1, 1, 2, co)
+    x = torch.tensor([3.0, -2.0], device="cuda").view(1, 1, 1, 2, 1)
+    dW, db = torch.full((3, 3, 3, 1, co), float("nan"), device="cuda"), torch.full((co,), float("nan"), device="cuda")
+    ws = torch.empty(k3.conv3d_bwd_weight_workspace_bytes(x, g), device="cuda", dtype=torch.uint8)
+    k3.conv3d_bwd_weight(x, g, None, dW, db, ws)
+    want = torch.zeros_like(dW)      # whole numbers below 2^24: exact
+    g0, g1 = g[0, 0, 0, 0], g[0, 0, 0, 1]
+    want[1, 1, 0, 0], want[1, 1, 1, 0], want[1, 1, 2, 0] = 3.0 * g1, 3.0 * g0 - 2.0 * g1, -2.0 * g0
+    assert torch.equal(dW, want) and torch.equal(db, g0 + g1)
