@@ -224,7 +224,11 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
             const int off = ((tap / 9) * HH + (tap / 3) % 3) * HW * PITCH + (tap % 3) * PITCH + sl * 4;
             f32x4 x[NB];
 #pragma unroll
-            for (int b = 0; b < NB; ++b) x[b] = *reinterpret_cast<const f32x4 *>(xs + vb[b] + off);
+            for (int b = 0; b < NB; ++b) {
+                x[b] = *reinterpret_cast<const f32x4 *>(xs + vb[b] + off);
+                // slots behind the last tap: zeros on both sides, or an infinite input would make them NaN
+                if (S < 4 && i == MYSTEPS - 1 && q >= 27 * S) x[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll

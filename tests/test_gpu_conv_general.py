@@ -132,3 +132,27 @@ def test_weight_gradient_of_more_blocks_than_a_grid_axis_has():
     g0, g1 = g[0, 0, 0, 0], g[0, 0, 0, 1]
     want[1, 1, 0, 0], want[1, 1, 1, 0], want[1, 1, 2, 0] = 3.0 * g1, 3.0 * g0 - 2.0 * g1, -2.0 * g0
     assert torch.equal(dW, want) and torch.equal(db, g0 + g1)
+
+
+@pytest.mark.parametrize("ch", [1, 4, 5, 8])      # one and two slots a voxel, with and without quads
+@pytest.mark.parametrize("size", [(4, 4, 8), (33, 28, 39)])      # split contraction, 128-voxel tiles
+def test_an_infinite_input_stays_infinite(orc, ch, size):
+    import torch
+    from paper_1811_12174_amd import k3
+    from gpu_util import to_dev, to_f64, empty
+    sp = (1,) + size
+    for v in (np.inf, -np.inf):
+        x, w = synth.activations(630, sp + (ch,), "f32"), synth.conv_weights(631, ch, 8, "f32")
+        x[0, 2, 1, 3, ch - 1] = v
+        y = empty(sp + (8,), "f32")
+        k3.conv3d_fwd(to_dev(x, "f32"), to_dev(w, "f32"), None, None, 0, y)
+        g, wb = synth.activations(632, sp + (ch,), "f32"), synth.conv_weights(633, 8, ch, "f32")
+        g[0, 1, 2, 5, 0] = v
+        dx = empty(sp + (8,), "f32")
+        k3.conv3d_bwd_data(to_dev(g, "f32"), None, to_dev(wb, "f32"), None, dx)
+        torch.cuda.synchronize()
+        for got, ref in ((to_f64(y), orc.conv3d_fwd(x.astype(np.float64), w.astype(np.float64), np.zeros(8), relu=False)),
+                         (to_f64(dx), orc.conv3d_bwd_data(g.astype(np.float64), wb.astype(np.float64)))):
+            inf = np.isinf(ref)
+            assert inf.sum() == 27 * 8 and not np.isnan(ref).any()
+            assert np.array_equal(got[inf], ref[inf]) and np.isfinite(got[~inf]).all()
