@@ -16,7 +16,9 @@ the memory high-water mark is a property of the program and the budget, not of t
     for that tensor's outgoing copy.  With `eager=True` it is dropped at once.
   * free of a tensor whose outgoing copy may still run leaves its range of the slab alone until an
     allocation needs it (these ranges go before any droppable tensor) or the run ends; only then
-    does the compute stream wait for that copy.
+    does the compute stream wait for that copy.  Allocations fall into other holes by that, and
+    under a tight budget the holes may then not line up: with `linger=False` the range is free at
+    once, and the compute stream waits at once (planner.lingers says which of the two a plan takes).
   * prefetch brings a dropped tensor back into a fresh block (`prefetch_start`: the copy
     overlaps the kernels enqueued after it); a tensor that was never dropped is simply kept.
   * wait fences the compute stream behind the copy-in, right before the first reader.
@@ -100,9 +102,10 @@ class Executor:
          swap_out(info, block) -> handle, release_after(handle), prefetch_start(handle, block),
          wait_in(handle), evict(handle), release(handle)"""
 
-    def __init__(self, backend, program, budget=None, eager=False, fixed_bytes=0):
+    def __init__(self, backend, program, budget=None, eager=False, fixed_bytes=0, linger=True):
         self.be, self.prog = backend, program
         self.budget, self.eager, self.fixed = budget, eager, fixed_bytes
+        self.linger = linger and budget is not None
         self.used = fixed_bytes
         self.peak = fixed_bytes
         self.arena = None if budget is None else Arena(budget - fixed_bytes)
@@ -211,7 +214,7 @@ class Executor:
             if t in self._droppable:
                 self._droppable.remove(t)
             if self._where.pop(t, None) == "device":
-                if self.arena is not None:
+                if self.linger:
                     self._lingering.append((t, h, self._blocks.pop(t), self._off.pop(t)))
                     return
                 self.be.release_after(h)     # the block may be reused from here on

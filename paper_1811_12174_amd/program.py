@@ -59,8 +59,9 @@ class Program:
         self.calls = []
         self._pending_allocs = []
         self.keep = set()
-        # derived once per program by its users: scratch bytes of its calls, native call lists, default swap plans
-        self.workspace, self.lists, self.plans = None, {}, {}
+        # derived once per program by its users: scratch bytes of its calls, native call lists, default swap
+        # plans, and how a plan's freed ranges are treated
+        self.workspace, self.lists, self.plans, self.lingers = None, {}, {}, {}
 
     # ---- construction
     def external(self, name, shape, ebytes=None):

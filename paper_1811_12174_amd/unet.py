@@ -331,7 +331,9 @@ class StepNet:
         if plan is None and budget is None and not (keep_acts or timing or self.copies_only) and x.is_contiguous() and x.dtype == self.dtype:
             return self._step_list(prog, x, labels)
         ins = prog.instructions(plan.gaps, plan.lead, plan.at) if plan is not None else prog.instructions()
-        ex = Executor(self, prog, budget=budget, eager=bool(plan is not None and plan.eager), fixed_bytes=self.fixed_bytes(prog))
+        fixed = self.fixed_bytes(prog)
+        linger = plan is not None and budget is not None and planner.lingers(prog, plan, budget, fixed)
+        ex = Executor(self, prog, budget=budget, eager=bool(plan is not None and plan.eager), fixed_bytes=fixed, linger=linger)
         self._timing = [] if timing else None
         if timing:
             start = torch.cuda.Event(enable_timing=True)
