@@ -302,8 +302,9 @@ int k3_probe_copy(const void *src, void *dst, size_t bytes, int blocks, void *st
  * can be reused; before its backward consumer runs it is copied back.
  *
  * A handle walks RESIDENT -> OUT_IN_FLIGHT -> ON_HOST -> IN_IN_FLIGHT -> RESIDENT; calls
- * that do not fit the current state return K3_E_STATE.  The contexts of a device share two
- * copy streams (device-to-host, host-to-device); each owns its events.  Host buffers are owned by
+ * that do not fit the current state return K3_E_STATE.  A context has two copy streams
+ * (device-to-host, host-to-device), shared with the contexts whose copies wait for the same
+ * compute stream, and events of its own.  Host buffers are owned by
  * the caller, must be page-locked (K3_E_NOT_PINNED otherwise) and must stay valid
  * until the handle is released.  Calls on one context must come from one thread. */
 typedef struct k3_lms k3_lms;
@@ -356,7 +357,7 @@ int k3_lms_evict(k3_lms *ctx, int handle, void *stream);
  * k3_lms_release_after) is waited for first, so the host buffer may be reused or freed
  * once this returns. */
 int k3_lms_release(k3_lms *ctx, int handle);
-/* Blocks the host until both copy streams (the device's, see above) are idle. */
+/* Blocks the host until the context's copies are done and both its copy streams are idle. */
 int k3_lms_sync(k3_lms *ctx);
 
 typedef struct k3_lms_stats {

@@ -24,8 +24,7 @@ Engine::Engine(Backend *be, uint64_t budget) : be_(be), budget_(budget) {}
 
 Engine::~Engine()
 {
-    if (d2h_) be_->stream_sync(d2h_);
-    if (h2d_) be_->stream_sync(h2d_);
+    sync();
     for (Slot &s : slots_) {
         if (s.ev_ready) be_->event_destroy(s.ev_ready);
         if (s.ev_out) be_->event_destroy(s.ev_out);
@@ -82,6 +81,7 @@ int Engine::swap_out(const void *dev, size_t bytes, void *host, stream_t compute
 {
     if (!dev || !host || !handle || bytes == 0) return E_BADARG;
     if (!be_->is_pinned(host, bytes)) return E_NOT_PINNED;
+    BE(be_->copy_streams(compute, &d2h_, &h2d_));
     int h;
     if (!free_.empty()) {
         h = free_.back();
@@ -150,6 +150,7 @@ int Engine::prefetch_start(int handle, void *dev, stream_t block_stream)
     }
     // a copy-out still in flight is fine once the block was handed over: the copy-in waits for it
     if (s->state != ON_HOST && !(s->state == OUT_IN_FLIGHT && s->handed)) return E_STATE;
+    BE(be_->copy_streams(block_stream, &d2h_, &h2d_));
     BE(be_->event_record(s->ev_ready, block_stream));
     BE(be_->stream_wait_event(h2d_, s->ev_ready));
     BE(be_->stream_wait_event(h2d_, s->ev_out));  // no-op when the swap-out already finished
@@ -210,8 +211,12 @@ int Engine::release(int handle)
 
 int Engine::sync()
 {
-    BE(be_->stream_sync(d2h_));
-    BE(be_->stream_sync(h2d_));
+    for (Slot &s : slots_) {   // copies may still run on streams that were used before
+        if (s.state == OUT_IN_FLIGHT) BE(be_->event_sync(s.ev_out));
+        if (s.state == IN_IN_FLIGHT) BE(be_->event_sync(s.ev_in));
+    }
+    if (d2h_) BE(be_->stream_sync(d2h_));
+    if (h2d_) BE(be_->stream_sync(h2d_));
     return OK;
 }
 

@@ -22,6 +22,8 @@ struct Backend {
     virtual int stream_create(stream_t *s) = 0;
     virtual int stream_destroy(stream_t s) = 0;
     virtual int stream_sync(stream_t s) = 0;
+    // the copy streams for copies that wait for `compute` (left as they are: the ones made at the start)
+    virtual int copy_streams(stream_t compute, stream_t *d2h, stream_t *h2d) { (void)compute; (void)d2h; (void)h2d; return 0; }
     virtual int event_create(event_t *e) = 0;
     virtual int event_destroy(event_t e) = 0;
     virtual int event_record(event_t e, stream_t s) = 0;
@@ -44,7 +46,7 @@ class Engine {
 public:
     Engine(Backend *be, uint64_t device_budget_bytes);
     ~Engine();
-    int init();  // creates the two copy streams
+    int init();  // asks for the two copy streams
     int account_alloc(uint64_t bytes);
     int account_free(uint64_t bytes);
     int swap_out(const void *dev, size_t bytes, void *host, stream_t compute, int *handle);

@@ -1,11 +1,11 @@
 // HIP backend of the swap engine and the k3_lms_* C-ABI entry points.  Copies run on two
 // dedicated non-blocking streams at the default priority (one per direction, so both DMA
-// directions can be busy at once) and are fenced with timing-disabled events.  The contexts of a
-// device share its two streams: they share its link anyway, and each further pair would take two
-// of the process's few hardware queues.
-#include <mutex>
+// directions can be busy at once) and are fenced with timing-disabled events; copy_pool.h says which
+// contexts share them.
 #include <new>
 #include <vector>
+
+#include "copy_pool.h"
 
 #include "common.h"
 #include "lms_engine.h"
@@ -25,17 +25,16 @@ __global__ __launch_bounds__(256) void lms_poison_kernel(unsigned char *p, size_
     }
 }
 
-// The copy streams of each device, made by its first context and destroyed with its last.  Contexts
-// may live on different threads: each call sequence (wait, copy, record) stays in order on the
-// stream whatever another thread enqueues in between, which can only make an event later.
-constexpr int kMaxDevices = 64;
-struct CopyStreams { hipStream_t st[2] = {nullptr, nullptr}; int users[2] = {0, 0}; };
-std::mutex g_copy_lock;
-CopyStreams g_copy[kMaxDevices];
+k3lms::CopyPool &copy_pool()
+{
+    static k3lms::CopyPool *pool = new k3lms::CopyPool;   // (never destroyed: contexts may outlive static objects)
+    return *pool;
+}
 
 struct HipBackend : k3lms::Backend {
     int last = 0;
-    int device = -1, made = 0;   // the device of this context's streams; the engine asks for device-to-host, then host-to-device
+    int device = -1;                    // current when the context was made: its copy streams live there
+    k3lms::CopyPair *pair = nullptr;
     // optional timing of the copies (off by default): a timed event pair around every copy; the
     // copies of a direction run one after the other on one stream, so the sum of the pairs is the
     // time that direction's copy engine was busy
@@ -71,6 +70,7 @@ struct HipBackend : k3lms::Backend {
     }
     int timed_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t st, int dir)
     {
+        std::lock_guard<std::mutex> g(pair->enqueue);   // no other context's work between the two events
         if (!timing) return chk(hipMemcpyAsync(dst, src, bytes, kind, st));
         hipEvent_t t0 = timed_event(), t1 = timed_event();
         if (!t0 || !t1) return chk(hipMemcpyAsync(dst, src, bytes, kind, st));
@@ -83,6 +83,13 @@ struct HipBackend : k3lms::Backend {
     }
     ~HipBackend()
     {
+        for (k3lms::CopyPair *p : copy_pool().give_back(pair, device)) {
+            for (k3lms::stream_t st : {p->d2h, p->h2d}) {
+                (void)hipStreamSynchronize((hipStream_t)st);
+                (void)hipStreamDestroy((hipStream_t)st);
+            }
+            delete p;
+        }
         for (Timed &t : pending) { (void)hipEventDestroy(t.t0); (void)hipEventDestroy(t.t1); }
         for (hipEvent_t e : spare) (void)hipEventDestroy(e);
     }
@@ -95,28 +102,32 @@ struct HipBackend : k3lms::Backend {
         }
         return 0;
     }
-    int stream_create(k3lms::stream_t *s) override
+    int stream_create(k3lms::stream_t *s) override   // the streams are known with the first copy's compute stream
     {
-        if (device < 0 && chk(hipGetDevice(&device))) return 1;
-        if (device >= kMaxDevices || made > 1) return 1;
-        std::lock_guard<std::mutex> g(g_copy_lock);
-        CopyStreams &c = g_copy[device];
-        if (!c.st[made] && chk(hipStreamCreateWithFlags(&c.st[made], hipStreamNonBlocking))) return 1;
-        *s = c.st[made];
-        ++c.users[made++];
-        return 0;
+        *s = nullptr;
+        return chk(hipGetDevice(&device));
     }
-    int stream_destroy(k3lms::stream_t s) override
+    int stream_destroy(k3lms::stream_t) override { return 0; }
+    int create_pair(k3lms::CopyPair &p)
     {
-        std::lock_guard<std::mutex> g(g_copy_lock);
-        for (int d = 0; d < 2; ++d) {
-            CopyStreams &c = g_copy[device];
-            if (c.st[d] != (hipStream_t)s) continue;
-            if (--c.users[d] > 0) return 0;
-            c.st[d] = nullptr;
-            return chk(hipStreamDestroy((hipStream_t)s));
-        }
-        return 1;
+        int now = device;
+        if (chk(hipGetDevice(&now)) || (now != device && chk(hipSetDevice(device)))) return 1;
+        hipStream_t st[2] = {nullptr, nullptr};
+        int rc = 0;
+        for (hipStream_t &one : st) rc = rc || chk(hipStreamCreateWithFlags(&one, hipStreamNonBlocking));
+        if (rc && st[0]) (void)hipStreamDestroy(st[0]);
+        p.d2h = st[0];
+        p.h2d = st[1];
+        return (now != device && chk(hipSetDevice(now))) || rc;
+    }
+    int copy_streams(k3lms::stream_t compute, k3lms::stream_t *d2h, k3lms::stream_t *h2d) override
+    {
+        k3lms::CopyPair *p = copy_pool().lease(pair, device, compute, [this](k3lms::CopyPair &n) { return create_pair(n); });
+        if (!p) return 1;
+        pair = p;
+        *d2h = p->d2h;
+        *h2d = p->h2d;
+        return 0;
     }
     int stream_sync(k3lms::stream_t s) override { return chk(hipStreamSynchronize((hipStream_t)s)); }
     int event_create(k3lms::event_t *e) override
@@ -130,6 +141,8 @@ struct HipBackend : k3lms::Backend {
     int event_record(k3lms::event_t e, k3lms::stream_t s) override { return chk(hipEventRecord((hipEvent_t)e, (hipStream_t)s)); }
     int stream_wait_event(k3lms::stream_t s, k3lms::event_t e) override
     {
+        std::unique_lock<std::mutex> g;
+        if (pair && (s == pair->d2h || s == pair->h2d)) g = std::unique_lock<std::mutex>(pair->enqueue);
         return chk(hipStreamWaitEvent((hipStream_t)s, (hipEvent_t)e, 0));
     }
     int event_query(k3lms::event_t e, bool *done) override

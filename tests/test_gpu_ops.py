@@ -290,3 +290,38 @@ def test_copy_busy_time_measurement():
     finally:
         k3.lms_host_free(host)
         k3.lms_destroy(ctx)
+
+
+def test_contexts_do_not_wait_for_each_other():
+    """A copy that waits for its own compute stream holds up neither another context's copies nor its sync."""
+    import torch
+    from paper_1811_12174_amd import k3
+    a, b = k3.lms_create(0), k3.lms_create(0)
+    n = 1 << 20
+    t = torch.randint(0, 255, (n,), device="cuda", dtype=torch.uint8)
+    host = k3.lms_host_alloc(n)
+    busy, sink = torch.cuda.Stream(), torch.zeros(1 << 20, device="cuda")
+
+    def work(iters):     # a register-resident loop on one workgroup
+        with torch.cuda.stream(busy):
+            k3.probe_mfma_bf16(iters, 1, sink)
+    try:
+        torch.cuda.synchronize()
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        work(1000)
+        e0.record(busy)
+        work(100000)
+        e1.record(busy)
+        torch.cuda.synchronize()
+        work(int(100000 * 300 / e0.elapsed_time(e1)))      # 300 ms
+        h = k3.lms_swap_out(a, t.data_ptr(), n, host, busy.cuda_stream)
+        k3.lms_sync(b)
+        assert k3.lms_swap_out_done(a, h) == 0
+        k3.lms_sync(a)
+        assert k3.lms_swap_out_done(a, h) == 1
+        k3.lms_release(a, h)
+    finally:
+        torch.cuda.synchronize()
+        k3.lms_host_free(host)
+        k3.lms_destroy(a)
+        k3.lms_destroy(b)
