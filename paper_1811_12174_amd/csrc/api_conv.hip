@@ -233,7 +233,7 @@ static int bwd_weight_run(const k3_tensor *xd, const void *x, const k3_tensor *x
     if (mfma_ok(a.dtype, a.c1, a.c2, a.cout)) return conv_wgrad_mfma(a, dW, db, (float *)ws, (hipStream_t)stream);
     if (conv_first_ok(a.dtype, a.c1, a.c2, a.cout)) return conv_first_wgrad(a, dW, db, (float *)ws, (hipStream_t)stream);
     if (conv_narrow_ok(a))
-        return conv_wgrad_narrow(a, dW, db, (float *)ws, conv_wgrad_general_sets(a.N, a.D, a.H, a.W, a.c1 + a.c2, a.cout), (hipStream_t)stream);
+        return conv_wgrad_narrow(a, dW, db, (float *)ws, conv_wgrad_general_sets(a.N, a.D, a.H, a.W), (hipStream_t)stream);
     return conv_wgrad_general(a, dW, db, (float *)ws, (hipStream_t)stream);
 }
 

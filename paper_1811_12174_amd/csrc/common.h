@@ -118,6 +118,19 @@ __device__ __forceinline__ void dma16_buf(unsigned lds_base, __amdgpu_buffer_rsr
                  ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 
+// n / d for 0 <= n < 2^31 by one 32 x 32 multiply: with 2^sh >= d the rounded-up 2^(32 + sh) / d - 2^32
+// is off by less than one part in 2^32, which cannot reach the next integer for such n.
+struct FastDiv {
+    unsigned d, m, sh;
+    static FastDiv of(unsigned d)
+    {
+        unsigned sh = 0;
+        while ((1ull << sh) < d) ++sh;
+        return {d, (unsigned)((((1ull << 32) * ((1ull << sh) - d)) / d) + 1), sh};
+    }
+    __device__ __forceinline__ unsigned quot(unsigned n) const { return (__umulhi(n, m) + n) >> sh; }
+};
+
 template <typename T> struct elem;
 template <> struct elem<float> {
     static __device__ __forceinline__ float ld(const float *p) { return *p; }

@@ -1,6 +1,7 @@
 // 3x3x3 convolution for the tensors the bf16 matrix-core kernels do not take -- fp32, and bf16 with
-// channel counts that are no multiple of 16 -- on v_mfma_f32_16x16x4_f32: forward, backward-data and
-// backward-weight for any channel counts, fp32 products and fp32 accumulation.
+// channel counts that are no multiple of 16 or tensors off their alignment -- on
+// v_mfma_f32_16x16x4_f32: forward and backward-data for any channel counts, backward-weight of bf16
+// tensors (of fp32 ones: wgrad_ordered.hip), fp32 products and fp32 accumulation.
 //
 // Bound: a 16x16x4 instruction occupies the matrix core for 32 clocks and needs one 4-byte
 // operand word per lane and side, so neither LDS nor L2 can be the limit; what counts is that
@@ -64,34 +65,41 @@ __device__ __forceinline__ f32x4 load_quad_buf(const QuadSrc &s, int c1, int c2,
     return v;
 }
 
-// GEMM D[output channel][voxel] = sum over (tap, channel); A = weights, B = activations.  A lane
-// group of 16 lanes carries one 16-byte slot (4 channels of one tap) of a step, and the step's four
-// matrix instructions take channel 0..3 of the slot: the contraction order is permuted alike on
-// both sides.  S = slots per voxel and chunk (4: 16 channels and a step is a tap; 2 and 1: the 8 or
-// 4 channels of a narrow layer, and a step covers two or four taps, so narrow inputs cost no
-// padding).  The halo tile of a chunk sits in LDS (pitch of an odd number of slots at S = 4: the 16
-// lanes of a group then hit 16 different bank quads), the next chunk's in registers; weights come
-// straight from global memory (L2: a step multiplies for 128 clocks or more per fragment).
-// WN waves share the tile's voxels, the other factor of 4 splits the steps: volumes too small to
-// give each CU a 128-voxel tile take 32-voxel tiles whose four waves split the contraction and add
-// their sums through LDS in a fixed order.
-// One output block takes 128 registers, so that four workgroups share a CU: 16 -> 16 channels at 48^3
-// (864 workgroups, of which 768 fitted before and the rest ran alone) 27.2 -> 24.5 us.
-// BUF: tensors and weights are read through buffer descriptors (channel counts in whole quads on quad
-// boundaries, a tile's span below 2 GiB); else element by element.
-template <typename T, int TD, int TH, int TW, int WN, int S, int MB, bool BWD, bool BUF>
-__global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_kernel(GenConv<T> p)
+// GEMM D[output channel][voxel] = sum over (tap, channel); A = weights, B = activations.  One instruction
+// multiplies four neighbouring channels of one tap (lane group kg carries channel kg of them), and an
+// accumulator starts from the bias and takes the taps in the order of the definition and the channels
+// of a tap in theirs.  The instruction is a chain of four fused multiply-adds in lane-group order
+// (measured: equal to the bit over 65536 sums of four magnitudes, subnormal ones too), so every sum is the
+// plain loop over the definition with one rounding per term.  That order is kept on purpose: in fp32
+// networks any other one moves a few ReLU signs and pooling maxima out of millions, and with them whole
+// gradient elements (of the fp32 U-Net at 48^3 in one batch of six by more than 4e-5 of the norm).  So
+// neither the waves nor the workgroups split a sum: the waves of a workgroup take different
+// voxels (WN of them) and output channels, and all channels of the halo tile are in LDS at once.  Bound:
+// the chain of 27 K / 4 instructions of 32 clocks where a volume gives the chip only a wave or so per
+// SIMD, else the matrix core.  A step is U instructions on 4 U channels of a tap: U = 4 for channels in
+// whole 16s; U = 1 for any, padded to whole fours with zeros on both sides (which change no sum).  SPT:
+// steps a tap where that is known at compile time, else 0.  S: quads of a voxel that neighbouring threads
+// stage (1: at most 4 channels).  QUAD: activations are read through buffer descriptors (channel counts in
+// whole quads on quad boundaries, a tile's span below 2 GiB); else element by element.  LDS false: more
+// channels than LDS holds, or weights of 2 GiB and more: all operands come from memory one by one.
+template <int TD_, int TH_, int TW_, int WN_, int MB_>
+struct GenTile {
+    static constexpr int TD = TD_, TH = TH_, TW = TW_, WN = WN_, MB = MB_, WM = 4 / WN, NB = TD * TH * TW / 16 / WN, CO = 16 * MB * WM;
+    static constexpr int HD = TD + 2, HH = TH + 2, HW = TW + 2, NHALO = HD * HH * HW;
+};
+
+template <typename T, class C, int S, int U, int SPT, bool BWD, bool QUAD, bool LDS>
+__global__ __launch_bounds__(256, LDS ? 4 : 2) void conv_general_kernel(GenConv<T> p)
 {
-    constexpr int HD = TD + 2, HH = TH + 2, HW = TW + 2, NHALO = HD * HH * HW;
-    constexpr int PITCH = S == 4 ? 20 : S == 2 ? 12 : 4;        // floats per halo voxel
-    constexpr int WK = 4 / WN, NBLK = TD * TH * TW / 16, NB = NBLK / WN;
-    constexpr int NSTEP = (27 * S + 3) / 4, ITEMS = (NHALO * S + 255) / 256;
-    constexpr int RED = WK > 1 ? 4 * NBLK * MB * 256 : 0;
-    __shared__ __attribute__((aligned(16))) float xs[NHALO * PITCH > RED ? NHALO * PITCH : RED];
+    constexpr int TH = C::TH, TW = C::TW, HH = C::HH, HW = C::HW, NHALO = C::NHALO, NB = C::NB, MB = C::MB;
+    constexpr int ITEMS = (NHALO * S + 255) / 256, RING = U * NB * MB >= 16 ? 3 : 9, AHEAD = RING - 1;
+    constexpr int XRING = LDS ? 3 : RING, XAHEAD = XRING - 1;
+    static_assert(27 % RING == 0 && (U == 1 || QUAD), "whole turns of the ring; steps of 16 channels read quads");
+    extern __shared__ __attribute__((aligned(16))) float xs[];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = lane >> 4, ln = lane & 15;
-    const int wn = wv % WN, wk = wv / WN;
-    const int K = p.c1 + p.c2, M = p.cd1 + p.cd2;
+    const int wn = wv % C::WN, wm = wv / C::WN;
+    const int K = p.c1 + p.c2, M = p.cd1 + p.cd2, KP = (K + 3) & ~3, pitch = general_pitch(K);
 
     // consecutive workgroup ids go round the 8 XCDs: give each XCD a contiguous run of the logical
     // order, in which the channel groups of a tile are neighbours (they share its halo in the L2)
@@ -103,235 +111,331 @@ __global__ __launch_bounds__(256, !BUF ? 2 : MB == 1 ? 4 : 3) void conv_general_
     t /= p.ntw;
     const int h0 = (int)(t % p.nth) * TH;
     t /= p.nth;
-    const int d0 = (int)(t % p.ntd) * TD;
+    const int d0 = (int)(t % p.ntd) * C::TD;
     const int n = (int)(t / p.ntd);
-    const int m0 = cb * 16 * MB;
+    const int m0 = (cb * C::WM + wm) * 16 * MB;
 
-    // the lane's halo items: (voxel, quad) i = tid + 256 k; offset of the voxel from the halo tile's
-    // first one, negative outside the volume
-    TileOff<BUF> vo[ITEMS];
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-        const int vox = (tid + k * 256) / S;
-        const int lw = vox % HW, lh = (vox / HW) % HH, ld = vox / (HW * HH);
-        const unsigned gd = d0 + ld - 1, gh = h0 + lh - 1, gw = w0 + lw - 1;
-        vo[k] = vox < NHALO && gd < (unsigned)p.D && gh < (unsigned)p.H && gw < (unsigned)p.W ? tile_offset<TileOff<BUF>>(ld, lh, lw, p.H, p.W) : -1;
-    }
-    const int64_t halo0 = (((int64_t)n * p.D + d0 - 1) * p.H + h0 - 1) * p.W + w0 - 1;
-    const QuadSrc xsrc = {rsrc_of(p.src1 + halo0 * p.c1, 0x7ffffff0), rsrc_of((p.src2 ? p.src2 : p.src1) + halo0 * p.c2, 0x7ffffff0)};
-    const QuadSrc msrc = {rsrc_of((p.mask ? p.mask : p.src1) + halo0 * p.c1, 0x7ffffff0), xsrc.r2};
-
-    f32x4 st[ITEMS];
-    auto fetch = [&](int c) __attribute__((always_inline)) {
+    if constexpr (LDS) {
+        // the lane's halo items: (voxel, quad) i = tid + 256 k; offset of the voxel from the halo tile's
+        // first one, negative outside the volume
+        TileOff<QUAD> vo[ITEMS];
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            const int q = (tid + k * 256) % S;
-            if constexpr (BUF) {
-                st[k] = load_quad_buf<T>(xsrc, p.c1, p.c2, vo[k], c * 4 * S, 4 * S, q);
-                if (p.mask) st[k] = keep_positive(st[k], load_quad_buf<T>(msrc, p.c1, 0, vo[k], c * 4 * S, 4 * S, q));
-            } else {
-                st[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (vo[k] >= 0) {
-                    const int ch = c * 4 * S + q * 4;
-                    st[k] = load_quad(p.src1, p.src2, p.c1, p.c2, halo0 + vo[k], ch);
-                    if (p.mask) st[k] = keep_positive(st[k], load_quad<T>(p.mask, nullptr, p.c1, 0, halo0 + vo[k], ch));
-                }
-            }
+            const int vox = (tid + k * 256) / S;
+            const int lw = vox % HW, lh = (vox / HW) % HH, ld = vox / (HW * HH);
+            const unsigned gd = d0 + ld - 1, gh = h0 + lh - 1, gw = w0 + lw - 1;
+            vo[k] = vox < NHALO && gd < (unsigned)p.D && gh < (unsigned)p.H && gw < (unsigned)p.W ? tile_offset<TileOff<QUAD>>(ld, lh, lw, p.H, p.W) : -1;
         }
-    };
-    // Weights of step s: the lane (row ln, slot kg) takes the four channels of its slot.  Rows and
-    // channels beyond the layer's get a lane offset outside the descriptor's range and read as zero, as
-    // do taps where a lane's offset holds the tap; where the tap is in the scalar offset it is clamped
-    // (without a descriptor: all are read from a clamped place and replaced).
-    const __amdgpu_buffer_rsrc_t wrsrc = rsrc_of(p.w, BUF ? 27 * K * M * (int)sizeof(T) : 0);
-    int lo[MB][4];               // element offset inside a tap, per chunk
-    bool keep[MB][4];
-    auto weights_chunk = [&](int c, int ln, int kg) __attribute__((always_inline)) {
+        const int64_t halo0 = (((int64_t)n * p.D + d0 - 1) * p.H + h0 - 1) * p.W + w0 - 1;
+        const QuadSrc xsrc = {rsrc_of(p.src1 + halo0 * p.c1, 0x7ffffff0), rsrc_of((p.src2 ? p.src2 : p.src1) + halo0 * p.c2, 0x7ffffff0)};
+        const QuadSrc msrc = {rsrc_of((p.mask ? p.mask : p.src1) + halo0 * p.c1, 0x7ffffff0), xsrc.r2};
+        constexpr int ROUND = ITEMS > 4 ? 2 : ITEMS > 2 ? 3 : 6;     // chunks in flight at once
+        f32x4 st[ROUND][ITEMS];
+        auto fetch = [&](int c, f32x4 (&to)[ITEMS]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int m = m0 + mb * 16 + ln, mc = m < M ? m : M - 1;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int k = c * 4 * S + (S == 4 ? kg : kg % S) * 4 + j, kc = k < K ? k : K - 1;
-                keep[mb][j] = m < M && k < K;
-                lo[mb][j] = BUF && !keep[mb][j] ? -1 : BWD ? mc * K + kc : kc * M + mc;
-            }
-        }
-    };
-    auto weights = [&](int s, float (&a)[MB][4]) __attribute__((always_inline)) {
-        const int tap = general_tap(S, s, kg);
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            if constexpr (BUF) {
-                // a step that is one tap has a wave-uniform offset, else the lane's own is added
-                const int toff = (BWD ? 26 - tap : tap) * K * M;
-                const int soff = general_weight_soff<int>(S, s, BWD, K, M, (int)sizeof(T));
-                auto at = [&](int o) __attribute__((always_inline)) { return S == 4 ? o : o < 0 || tap > 26 ? -1 : o + toff; };
-                if constexpr (BWD) {   // the contraction runs along the fastest axis: one load
-                    const f32x4 v = buf<T>::quad(wrsrc, at(lo[mb][0]), soff);
-                    a[mb][0] = v[0]; a[mb][1] = v[1]; a[mb][2] = v[2]; a[mb][3] = v[3];
+            for (int k = 0; k < ITEMS; ++k) {
+                const int q = (tid + k * 256) % S;
+                if constexpr (QUAD) {
+                    to[k] = load_quad_buf<T>(xsrc, p.c1, p.c2, vo[k], c * 4 * S, 4 * S, q);
+                    if (p.mask) to[k] = keep_positive(to[k], load_quad_buf<T>(msrc, p.c1, 0, vo[k], c * 4 * S, 4 * S, q));
                 } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) a[mb][j] = buf<T>::one(wrsrc, at(lo[mb][j]), soff);
-                }
-            } else {
-                const int tc = tap < 27 ? tap : 26;
-                const T *wt = p.w + (int64_t)(BWD ? 26 - tc : tc) * K * M;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float v = elem<T>::ld(wt + lo[mb][j]);
-                    a[mb][j] = keep[mb][j] && tap < 27 ? v : 0.f;
+                    to[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (vo[k] >= 0) {
+                        const int ch = c * 4 * S + q * 4;
+                        to[k] = load_quad(p.src1, p.src2, p.c1, p.c2, halo0 + vo[k], ch);
+                        if (p.mask) to[k] = keep_positive(to[k], load_quad<T>(p.mask, nullptr, p.c1, 0, halo0 + vo[k], ch));
+                    }
                 }
             }
+        };
+        const int nchunk = (K + 4 * S - 1) / (4 * S);
+        for (int c = 0; c < nchunk; c += ROUND) {
+#pragma unroll
+            for (int r = 0; r < ROUND; ++r)
+                if (c + r < nchunk) fetch(c + r, st[r]);
+#pragma unroll
+            for (int r = 0; r < ROUND; ++r)
+#pragma unroll
+                for (int k = 0; k < ITEMS; ++k) {
+                    const int i = tid + k * 256, ch = (c + r) * 4 * S + (i % S) * 4;
+                    if (i < NHALO * S && ch < KP) *reinterpret_cast<f32x4 *>(xs + (i / S) * pitch + ch) = st[r][k];
+                }
         }
+        __syncthreads();
+    }
+    if (m0 >= M) return;
+
+    // Weights of (tap, four U channels from c on): the lane (row ln, lane group kg) takes channel kg of each
+    // four.  Rows beyond the layer's, and channels beyond it, get a lane offset outside the descriptor's range
+    // and read as zero (without a descriptor: both are read from a clamped place and replaced).
+    const __amdgpu_buffer_rsrc_t wrsrc = rsrc_of(p.w, LDS ? 27 * K * M * (int)sizeof(T) : 0);
+    int lo[MB][U];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int m = m0 + mb * 16 + ln;
+            lo[mb][j] = m >= M || (S == 1 && kg >= K) ? -1 : BWD ? m * K + kg * U + j : (4 * j + kg) * M + m;
+        }
+    auto weights = [&](int tap, int c, float (&a)[MB][U]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                if constexpr (BWD && U == 4) {
+                    // a row's 16 channels lie together: the lane reads four and spread() deals them out (16 loads
+                    // of 16 bytes instead of 64 of 4: 16 -> 16 at 48^3 58 -> 25 us)
+                    if (j == 0) {
+                        const f32x4 v = buf<T>::quad(wrsrc, lo[mb][0], general_weight<int>(BWD, tap, c, K, M) * (int)sizeof(T));
+                        a[mb][0] = v[0]; a[mb][1] = v[1]; a[mb][2] = v[2]; a[mb][3] = v[3];
+                    }
+                } else if constexpr (LDS) {
+                    const int o = !QUAD && S > 1 && c + kg >= K ? -1 : lo[mb][j];
+                    a[mb][j] = buf<T>::one(wrsrc, o, general_weight<int>(BWD, tap, c, K, M) * (int)sizeof(T));
+                } else {
+                    const int m = m0 + mb * 16 + ln, ch = c + kg, mc = m < M ? m : M - 1, kc = ch < K ? ch : K - 1;
+                    const float v = elem<T>::ld(p.w + general_weight<int64_t>(BWD, tap, BWD ? 0 : kc, K, M) + (BWD ? (int64_t)mc * K + kc : mc));
+                    a[mb][j] = m < M && ch < K ? v : 0.f;
+                }
+            }
     };
-    int vb[NB];   // LDS index of the lane's voxel in each 16-voxel block, tap (0,0,0)
+    struct Place {      // in the sum: tap and first channel
+        int tap, c;
+    };
+    auto advance = [&](Place &q) __attribute__((always_inline)) { general_next(q.tap, q.c, 4 * U, KP); };
+    int vb[NB];   // LDS index of the lane's voxel and channel in each 16-voxel block, halo position (0,0,0)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int i = (wn * NB + b) * 16 + ln;
-        vb[b] = (((i / (TW * TH)) * HH + (i / TW) % TH) * HW + i % TW) * PITCH;
+        vb[b] = (((i / (TW * TH)) * HH + (i / TW) % TH) * HW + i % TW) * pitch + kg;
     }
+    auto inputs = [&](const Place &q, float (&x)[NB][U]) __attribute__((always_inline)) {
+        const int c = q.c, pos = BWD ? 26 - q.tap : q.tap;     // place of the tap's voxel in the halo
+        if constexpr (LDS) {
+            const int off = (((pos / 9) * HH + (pos / 3) % 3) * HW + pos % 3) * pitch + c;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < U; ++j) x[b][j] = xs[vb[b] + off + 4 * j];
+        } else {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int i = (wn * NB + b) * 16 + ln, ch = c + kg;
+                const unsigned gd = d0 + i / (TW * TH) + pos / 9 - 1, gh = h0 + (i / TW) % TH + (pos / 3) % 3 - 1, gw = w0 + i % TW + pos % 3 - 1;
+                x[b][0] = 0.f;
+                if (gd < (unsigned)p.D && gh < (unsigned)p.H && gw < (unsigned)p.W && ch < K) {
+                    const int64_t v = (((int64_t)n * p.D + gd) * p.H + gh) * p.W + gw;
+                    x[b][0] = ch < p.c1 ? elem<T>::ld(p.src1 + v * p.c1 + ch) : elem<T>::ld(p.src2 + v * p.c2 + (ch - p.c1));
+                    if (p.mask && !(elem<T>::ld(p.mask + v * p.c1 + ch) > 0.f)) x[b][0] = 0.f;
+                }
+            }
+        }
+    };
     f32x4 acc[NB][MB];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[b][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int nchunk = (K + 4 * S - 1) / (4 * S);
-    constexpr int MYSTEPS = (NSTEP + WK - 1) / WK, AHEAD = 2;   // weights travel this many steps ahead
-    fetch(0);
-    for (int c = 0; c < nchunk; ++c) {
-        if (c > 0) __syncthreads();   // every wave is done with the chunk before
-        int tl = tid;
-        asm("" : "+v"(tl));           // addresses are worked out anew for each chunk: kept across the steps they cost the occupancy
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            const int i = tl + k * 256;
-            if (i < NHALO * S) *reinterpret_cast<f32x4 *>(xs + (i / S) * PITCH + (i % S) * 4) = st[k];
-        }
-        float a[AHEAD + 1][MB][4];
-        weights_chunk(c, tl & 15, (tl & 63) >> 4);
-#pragma unroll
-        for (int i = 0; i < AHEAD; ++i) weights(i * WK + wk, a[i]);
-        if (c + 1 < nchunk) fetch(c + 1);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MYSTEPS; ++i) {
-            const int s = i * WK + wk;
-            if (NSTEP % WK != 0 && i == MYSTEPS - 1 && s >= NSTEP) break;      // wave-uniform
-            if (i + AHEAD < MYSTEPS) weights(s + AHEAD * WK, a[(i + AHEAD) % (AHEAD + 1)]);
-            const int q = 4 * s + kg, tap = S == 4 ? s : (q / S < 27 ? q / S : 26), sl = S == 4 ? kg : q % S;
-            const int off = ((tap / 9) * HH + (tap / 3) % 3) * HW * PITCH + (tap % 3) * PITCH + sl * 4;
-            f32x4 x[NB];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                x[b] = *reinterpret_cast<const f32x4 *>(xs + vb[b] + off);
-                // slots behind the last tap: zeros on both sides, or an infinite input would make them NaN
-                if (S < 4 && i == MYSTEPS - 1 && q >= 27 * S) x[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int r = 0; r < 4; ++r) {
+                const int m = m0 + mb * 16 + kg * 4 + r;
+                acc[b][mb][r] = p.bias && m < M ? p.bias[m] : 0.f;
             }
+
+    auto multiply = [&](float (&as)[MB][U], float (&xr)[NB][U]) __attribute__((always_inline)) {
+        if constexpr (BWD && U == 4) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int mb = 0; mb < MB; ++mb) spread(as[mb]);
+        }
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+        for (int j = 0; j < U; ++j)
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb) acc[b][mb] = mfma_f32(a[i % (AHEAD + 1)][mb][j], x[b][j], acc[b][mb]);
-            __builtin_amdgcn_sched_barrier(0);   // no further ahead: hoisted loads cost the occupancy
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[b][mb] = mfma_f32(as[mb][j], xr[b][j], acc[b][mb]);
+    };
+    if constexpr (SPT > 0) {
+        // SPT steps a tap, known at compile time (4 U SPT channels): a turn is one row of taps (the three rows of a
+        // plane where a row is only a few steps), everything inside it at constant offsets.  A wave alone on
+        // its SIMD pays four clocks for every instruction, and the counting of the other form cost more
+        // than the matrix instructions (64 -> 64 at 12^3: 14.5 us against 20, 16 -> 16 at 48^3 24.6 against 29.3).
+        constexpr int ROWS = SPT <= (U == 1 ? 2 : 1) ? 3 : 1, ST = 3 * SPT * ROWS, PT = general_pitch(4 * U * SPT);
+        constexpr int R = U * NB * MB >= 16 ? 3 : ST % 9 == 0 ? 9 : SPT == 2 ? 6 : 12, A = R - 1 < 8 ? R - 1 : 8;
+        float a[R][MB][U], x[3][NB][U];
+        auto row = [&](int g) __attribute__((always_inline)) {      // LDS offset of the turn's first row of taps
+            const int q = BWD ? (ROWS == 3 ? 2 : 8) - g : g;
+            return (ROWS == 3 ? q * HH : (q / 3) * HH + q % 3) * HW * PT;
+        };
+        auto load_w = [&](int g, int st, float (&as)[MB][U]) __attribute__((always_inline)) {
+            weights(g * 3 * ROWS + st / SPT, (st % SPT) * 4 * U, as);
+        };
+        auto load_x = [&](int at, int st, float (&xr)[NB][U]) __attribute__((always_inline)) {
+            const int r = st / (3 * SPT), w = (st / SPT) % 3;
+            const int off = ((ROWS == 3 ? (BWD ? 2 - r : r) * HW : 0) + (BWD ? 2 - w : w)) * PT + (st % SPT) * 4 * U;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < U; ++j) xr[b][j] = xs[vb[b] + at + off + 4 * j];
+        };
+        int at = row(0);
+#pragma unroll
+        for (int i = 0; i < A; ++i) load_w(0, i, a[i]);
+        load_x(at, 0, x[0]);
+        load_x(at, 1, x[1]);
+        for (int g = 0; g < 9 / ROWS; ++g) {
+            const int gn = g + 1 < 9 / ROWS ? g + 1 : g, next = row(gn);     // (behind the last turn it is read again)
+#pragma unroll
+            for (int i = 0; i < ST; ++i) {
+                load_w(i + A < ST ? g : gn, (i + A) % ST, a[(i + A) % R]);
+                load_x(i + 2 < ST ? at : next, (i + 2) % ST, x[(i + 2) % 3]);
+                multiply(a[i % R], x[i % 3]);
+                __builtin_amdgcn_sched_barrier(0);   // no further ahead: hoisted loads cost the occupancy
+            }
+            at = next;
+        }
+    } else {
+        float a[RING][MB][U], x[XRING][NB][U];
+        Place pa = {0, 0}, px = {0, 0};
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            weights(pa.tap, pa.c, a[i]);
+            advance(pa);
+            if (i < XAHEAD) {
+                inputs(px, x[i]);
+                advance(px);
+            }
+        }
+        const int steps = 27 * (KP / (4 * U));
+        for (int s = 0; s < steps; s += RING) {
+#pragma unroll
+            for (int i = 0; i < RING; ++i) {
+                weights(pa.tap, pa.c, a[(i + AHEAD) % RING]);
+                advance(pa);
+                inputs(px, x[(i + XAHEAD) % XRING]);
+                advance(px);
+                multiply(a[i], x[i % XRING]);
+                __builtin_amdgcn_sched_barrier(0);   // no further ahead: hoisted loads cost the occupancy
+            }
         }
     }
 
     // a lane holds output channels m .. m+3 of one voxel of a block
-    auto emit = [&](int blk, int mb, f32x4 v) __attribute__((always_inline)) {
-        const int i = blk * 16 + ln;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int i = (wn * NB + b) * 16 + ln;
         const int gd = d0 + i / (TW * TH), gh = h0 + (i / TW) % TH, gw = w0 + i % TW;
-        const int m = m0 + mb * 16 + kg * 4;
-        if (gd >= p.D || gh >= p.H || gw >= p.W || m >= M) return;
+        if (gd >= p.D || gh >= p.H || gw >= p.W) continue;
         const int64_t vox = (((int64_t)n * p.D + gd) * p.H + gh) * p.W + gw;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float x = v[r] + (p.bias && m + r < M ? p.bias[m + r] : 0.f);
-            v[r] = (p.relu && !(x > 0.f)) ? 0.f : x;
-        }
-        if (p.vout) {
-            const bool d1 = m < p.cd1;
-            const int64_t o = d1 ? vox * p.cd1 + m : vox * p.cd2 + (m - p.cd1);
-            if (d1 && p.omask) v = keep_positive(v, buf<T>::ld4(p.omask + o));
-            buf<T>::st4((d1 ? p.dst1 : p.dst2) + o, v);
-        } else {
+        for (int mb = 0; mb < MB; ++mb) {
+            const int m = m0 + mb * 16 + kg * 4;
+            if (m >= M) continue;
+            f32x4 v = acc[b][mb];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int mm = m + r;
-                if (mm < p.cd1) {
-                    const int64_t o = vox * p.cd1 + mm;
-                    elem<T>::st(p.dst1 + o, p.omask && !(elem<T>::ld(p.omask + o) > 0.f) ? 0.f : v[r]);
-                } else if (mm < M) {
-                    elem<T>::st(p.dst2 + vox * p.cd2 + (mm - p.cd1), v[r]);
+            for (int r = 0; r < 4; ++r) v[r] = (p.relu && !(v[r] > 0.f)) ? 0.f : v[r];
+            if (p.vout) {
+                const bool d1 = m < p.cd1;
+                const int64_t o = d1 ? vox * p.cd1 + m : vox * p.cd2 + (m - p.cd1);
+                if (d1 && p.omask) v = keep_positive(v, buf<T>::ld4(p.omask + o));
+                buf<T>::st4((d1 ? p.dst1 : p.dst2) + o, v);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int mm = m + r;
+                    if (mm < p.cd1) {
+                        const int64_t o = vox * p.cd1 + mm;
+                        elem<T>::st(p.dst1 + o, p.omask && !(elem<T>::ld(p.omask + o) > 0.f) ? 0.f : v[r]);
+                    } else if (mm < M) {
+                        elem<T>::st(p.dst2 + vox * p.cd2 + (mm - p.cd1), v[r]);
+                    }
                 }
             }
-        }
-    };
-    if constexpr (WK == 1) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) emit(wn * NB + b, mb, acc[b][mb]);
-    } else {
-        static_assert(WN == 1 || WK == 1, "the waves split either the voxels or the contraction");
-        __syncthreads();
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) *reinterpret_cast<f32x4 *>(xs + (((wv * NBLK + b) * MB + mb) * 64 + lane) * 4) = acc[b][mb];
-        __syncthreads();
-        for (int q = wv; q < NBLK * MB; q += 4) {
-            f32x4 s = *reinterpret_cast<const f32x4 *>(xs + (q * 64 + lane) * 4);
-#pragma unroll
-            for (int k = 1; k < 4; ++k) s += *reinterpret_cast<const f32x4 *>(xs + ((k * NBLK * MB + q) * 64 + lane) * 4);
-            emit(q / MB, q % MB, s);
         }
     }
 }
 
-template <typename T, int TD, int TH, int TW, int WN, int S, int MB, bool BWD, bool BUF>
+template <typename T, class C, int S, int U, int SPT, bool BWD, bool QUAD, bool LDS = true>
 static int launch_general(GenConv<T> p, hipStream_t st)
 {
-    p.ntd = (p.D + TD - 1) / TD;
-    p.nth = (p.H + TH - 1) / TH;
-    p.ntw = (p.W + TW - 1) / TW;
-    p.ncb = (p.cd1 + p.cd2 + 16 * MB - 1) / (16 * MB);
+    p.ntd = (p.D + C::TD - 1) / C::TD;
+    p.nth = (p.H + C::TH - 1) / C::TH;
+    p.ntw = (p.W + C::TW - 1) / C::TW;
+    p.ncb = (p.cd1 + p.cd2 + C::CO - 1) / C::CO;
     p.total = (int64_t)p.N * p.ntd * p.nth * p.ntw * p.ncb;
     p.per_xcd = (p.total + 7) / 8;
     if (p.per_xcd * 8 > 0x7fffffffLL) return K3_E_UNSUPPORTED;
-    conv_general_kernel<T, TD, TH, TW, WN, S, MB, BWD, BUF><<<dim3((unsigned)(p.per_xcd * 8)), 256, 0, st>>>(p);
+    const int lds = LDS ? C::NHALO * general_pitch(p.c1 + p.c2) * (int)sizeof(float) : 0;
+    if (lds > 64 * 1024) {
+        static bool attr_done = false;  // raising the dynamic LDS limit is idempotent
+        if (!attr_done) {
+            K3_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_general_kernel<T, C, S, U, SPT, BWD, QUAD, LDS>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+            attr_done = true;
+        }
+    }
+    conv_general_kernel<T, C, S, U, SPT, BWD, QUAD, LDS><<<dim3((unsigned)(p.per_xcd * 8)), 256, lds, st>>>(p);
     K3_LAUNCH_CHECK();
     return K3_OK;
 }
 
 static uintptr_t bits(const void *p) { return (uintptr_t)p; }
 
-// 128-voxel tiles with two output blocks per workgroup where that gives every CU one, else with
-// one, else 32-voxel tiles (16 -> 16 channels at 12^3: 27 workgroups of the large kind)
-template <typename T, int S, bool BWD>
-static int launch_general_size(GenConv<T> p, hipStream_t st)
+// The largest tile that gives every CU a workgroup, with two output blocks a wave where that still does;
+// its halo must fit LDS twice (a workgroup then stages while another multiplies), the smallest tile's
+// once.  Volumes too small for that: 32 voxels x 32 channels a workgroup (64 x 16 of a 16-channel layer).
+template <typename T, int S, int U, int SPT, bool BWD, bool QUAD>
+static int launch_general_size(const GenConv<T> &p, hipStream_t st)
 {
-    const int64_t M = p.cd1 + p.cd2, K = p.c1 + p.c2, C = K > M ? K : M;
-    const int64_t big = (int64_t)p.N * ((p.D + 3) / 4) * ((p.H + 3) / 4) * ((p.W + 7) / 8);
-    // (of the weights only backward-data reads quads)
-    const bool buf = whole_quads(p.c1 | p.c2, bits(p.src1) | bits(p.src2) | bits(p.mask) | (BWD ? bits(p.w) : 0), sizeof(T)) &&
-                     6 * (int64_t)(p.H + 1) * p.W * C * 4 < 0x7fffffffLL && 27 * K * M * 4 < 0x7fffffffLL;
-    p.vout = whole_quads(p.cd1 | p.cd2, bits(p.dst1) | bits(p.dst2) | bits(p.omask), sizeof(T));
-    if (!buf) return launch_general<T, 4, 4, 8, 4, S, 1, BWD, false>(p, st);
-    if (M > 16 && big * ((M + 31) / 32) >= 256) return launch_general<T, 4, 4, 8, 4, S, 2, BWD, true>(p, st);
-    if (big * ((M + 15) / 16) >= 256) return launch_general<T, 4, 4, 8, 4, S, 1, BWD, true>(p, st);
-    return launch_general<T, 2, 4, 4, 1, S, 1, BWD, true>(p, st);
+    const int64_t M = p.cd1 + p.cd2;
+    auto groups = [&](int td, int th, int tw, int co) {
+        return (int64_t)p.N * ((p.D + td - 1) / td) * ((p.H + th - 1) / th) * ((p.W + tw - 1) / tw) * ((M + co - 1) / co);
+    };
+    const int64_t voxel = general_pitch(p.c1 + p.c2) * (int64_t)sizeof(float), half = 80 * 1024;
+    typedef GenTile<4, 4, 8, 4, 1> T1;
+    typedef GenTile<2, 4, 8, 4, 1> T2;
+    typedef GenTile<2, 4, 4, 2, 1> T3;
+    typedef GenTile<2, 2, 4, 1, 1> T4;
+    if constexpr (U * SPT < 16) {        // (a tile that 4 U SPT channels never fit, or never need, is not built)
+        if (T1::NHALO * voxel <= half) {
+            if constexpr (QUAD)
+                if (M > 16 && groups(4, 4, 8, 32) >= 256) return launch_general<T, GenTile<4, 4, 8, 4, 2>, S, U, SPT, BWD, QUAD>(p, st);
+            if (groups(4, 4, 8, 16) >= 256) return launch_general<T, T1, S, U, SPT, BWD, QUAD>(p, st);
+        }
+    }
+    if constexpr (U * SPT < 32) {
+        if (T2::NHALO * voxel <= half) {
+            if constexpr (QUAD)
+                if (M > 16 && groups(2, 4, 8, 32) >= 256) return launch_general<T, GenTile<2, 4, 8, 4, 2>, S, U, SPT, BWD, QUAD>(p, st);
+            if (M <= 16 || groups(2, 4, 8, 16) >= 256) return launch_general<T, T2, S, U, SPT, BWD, QUAD>(p, st);
+        }
+    }
+    if (T3::NHALO * voxel <= half) return launch_general<T, T3, S, U, SPT, BWD, QUAD>(p, st);
+    if constexpr (S == 4 && SPT == 0)
+        if (T4::NHALO * voxel <= 160 * 1024) return launch_general<T, T4, S, U, SPT, BWD, QUAD>(p, st);
+    if constexpr (SPT > 0) return K3_E_UNSUPPORTED;       // (not reached: up to 128 channels the third tile fits)
+    else return launch_general<T, T4, 4, 1, 0, BWD, false, false>(p, st);
 }
 
 template <typename T, bool BWD>
-static int launch_general_any(const GenConv<T> &p, hipStream_t st)
+static int launch_general_any(GenConv<T> p, hipStream_t st)
 {
-    const int K = p.c1 + p.c2;
-    if (K <= 4) return launch_general_size<T, 1, BWD>(p, st);
-    if (K <= 8) return launch_general_size<T, 2, BWD>(p, st);
-    return launch_general_size<T, 4, BWD>(p, st);
+    const int64_t M = p.cd1 + p.cd2, K = p.c1 + p.c2, C = K > M ? K : M;
+    const bool quad = whole_quads(p.c1 | p.c2, bits(p.src1) | bits(p.src2) | bits(p.mask), sizeof(T)) &&
+                      6 * (int64_t)(p.H + 1) * p.W * C * 4 < 0x7fffffffLL;
+    p.vout = whole_quads(p.cd1 | p.cd2, bits(p.dst1) | bits(p.dst2) | bits(p.omask), sizeof(T));
+    if (27 * K * M * 4 >= 0x7fffffffLL) return launch_general<T, GenTile<2, 2, 4, 1, 1>, 4, 1, 0, BWD, false, false>(p, st);
+    if (!quad && K <= 4) return launch_general_size<T, 1, 1, 1, BWD, false>(p, st);
+    if (!quad) return launch_general_size<T, 4, 1, 0, BWD, false>(p, st);
+    if (K == 4) return launch_general_size<T, 1, 1, 1, BWD, true>(p, st);
+    if (K == 8) return launch_general_size<T, 4, 1, 2, BWD, true>(p, st);
+    if (K % 16 || (BWD && !whole_quads(0, bits(p.w), sizeof(T)))) return launch_general_size<T, 4, 1, 0, BWD, true>(p, st);
+    if constexpr (sizeof(T) == 4) {      // (bf16 tensors of these get here by their alignment alone)
+        if (K == 16) return launch_general_size<T, 4, 4, 1, BWD, true>(p, st);
+        if (K == 32) return launch_general_size<T, 4, 4, 2, BWD, true>(p, st);
+        if (K == 64) return launch_general_size<T, 4, 4, 4, BWD, true>(p, st);
+        if (K == 128) return launch_general_size<T, 4, 4, 8, BWD, true>(p, st);
+    }
+    return launch_general_size<T, 4, 4, 0, BWD, true>(p, st);
 }
 
 template <typename T>
@@ -521,25 +625,24 @@ static GenWgradPlan general_wgrad_plan(int64_t N, int64_t D, int64_t H, int64_t 
     return q;
 }
 
-// The query promises at least one set of partial sums per 256 voxels, at most 1024 (more than the plan
-// takes for all but the smallest volumes): the size callers have allocated, and been refused by, so far.
-int64_t conv_wgrad_general_sets(int64_t N, int64_t D, int64_t H, int64_t W, int64_t cin, int64_t cout)
+// What the query promises, and no call takes more than: a set of partial sums per 256 voxels, at most 1024.
+int64_t conv_wgrad_general_sets(int64_t N, int64_t D, int64_t H, int64_t W)
 {
-    int64_t sets = N * D * H * W / 256;
-    if (sets > 1024) sets = 1024;
-    const int64_t need = general_wgrad_plan(N, D, H, W, cin, cout).nsplit;
-    return sets > need ? sets : need;
+    const int64_t sets = N * D * H * W / 256;
+    return sets < 1 ? 1 : sets > 1024 ? 1024 : sets;
 }
 size_t conv_wgrad_general_ws_bytes(int64_t N, int64_t D, int64_t H, int64_t W, int64_t cin, int64_t cout)
 {
-    return (size_t)conv_wgrad_general_sets(N, D, H, W, cin, cout) * (size_t)(27 * cin * cout + cout) * sizeof(float);
+    return (size_t)conv_wgrad_general_sets(N, D, H, W) * (size_t)(27 * cin * cout + cout) * sizeof(float);
 }
 
 template <typename T>
 static int wgrad_general_t(const ConvArgs &a, float *dW, float *db, float *ws, hipStream_t st)
 {
     const int64_t cin = a.c1 + a.c2;
-    const GenWgradPlan q = general_wgrad_plan(a.N, a.D, a.H, a.W, cin, a.cout);
+    GenWgradPlan q = general_wgrad_plan(a.N, a.D, a.H, a.W, cin, a.cout);
+    const int64_t most = conv_wgrad_general_sets(a.N, a.D, a.H, a.W);
+    if (q.nsplit > most) q.nsplit = most;
     const int64_t blocks = ((cin + 15) / 16) * ((a.cout + 15) / 16);
     if (q.nsplit * blocks > 0x7fffffffLL || q.tiles > 0x7fffffffLL) return K3_E_UNSUPPORTED;
     GenWgrad<T> p{};
@@ -568,7 +671,7 @@ static int wgrad_general_t(const ConvArgs &a, float *dW, float *db, float *ws, h
 }
 int conv_wgrad_general(const ConvArgs &a, float *dW, float *db, float *ws, hipStream_t st)
 {
-    return a.dtype == K3_F32 ? wgrad_general_t<float>(a, dW, db, ws, st) : wgrad_general_t<bf16_t>(a, dW, db, ws, st);
+    return a.dtype == K3_F32 ? conv_wgrad_ordered(a, dW, db, ws, st) : wgrad_general_t<bf16_t>(a, dW, db, ws, st);
 }
 
 }  // namespace k3

@@ -37,20 +37,20 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__res
 __device__ __forceinline__ void add4(float4 &s, const float4 &a) { s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w; }
 
 // Same sum for 16-byte aligned buffers whose element counts are multiples of 4: a thread adds float4
-// quads, 256 / G quads x G groups of splits per block, U loads in flight; the U chains and then the
-// groups are merged in a fixed order.  The last turn reads clamped places without a branch.
-template <int G>
+// quads, 256 / G quads x G groups of splits per block, U loads in flight for CH chains; the chains and
+// then the groups are merged in a fixed order.  The last turn reads clamped places without a branch.
+template <int G, int U = G == 16 ? 4 : 8, int CH = U>
 __global__ __launch_bounds__(256) void reduce_partials_vec4_kernel(const float4 *__restrict__ ws, float4 *__restrict__ dW,
                                                                   float4 *__restrict__ db, int64_t quadsW, int64_t quads,
                                                                   int nsplit)
 {
-    constexpr int Q = 256 / G, U = G == 16 ? 4 : 8;
+    constexpr int Q = 256 / G;
     __shared__ float4 part[G][Q];
     const int e = threadIdx.x % Q, g = threadIdx.x / Q;
     const int64_t i = (int64_t)blockIdx.x * Q + e;
-    float4 s[U];
+    float4 s[CH];
 #pragma unroll
-    for (int j = 0; j < U; ++j) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < CH; ++j) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < quads) {
         int k = g;
         for (; k + (U - 1) * G < nsplit; k += U * G) {
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void reduce_partials_vec4_kernel(const float4 
 #pragma unroll
             for (int j = 0; j < U; ++j) a[j] = ws[(int64_t)(k + j * G) * quads + i];
 #pragma unroll
-            for (int j = 0; j < U; ++j) add4(s[j], a[j]);
+            for (int j = 0; j < U; ++j) add4(s[j % CH], a[j]);
         }
         if (k < nsplit) {
             float4 a[U - 1];
@@ -66,11 +66,11 @@ __global__ __launch_bounds__(256) void reduce_partials_vec4_kernel(const float4 
             for (int j = 0; j < U - 1; ++j) a[j] = ws[(int64_t)(k + j * G < nsplit ? k + j * G : k) * quads + i];
 #pragma unroll
             for (int j = 0; j < U - 1; ++j)
-                if (k + j * G < nsplit) add4(s[j], a[j]);
+                if (k + j * G < nsplit) add4(s[j % CH], a[j]);
         }
     }
 #pragma unroll
-    for (int n = U / 2; n > 0; n /= 2)
+    for (int n = CH / 2; n > 0; n /= 2)
 #pragma unroll
         for (int j = 0; j < n; ++j) add4(s[j], s[j + n]);
     if (G > 1) {
@@ -86,12 +86,15 @@ __global__ __launch_bounds__(256) void reduce_partials_vec4_kernel(const float4 
     }
 }
 
+static bool reduce_quads(const float *ws, const float *dW, const float *db, int64_t countW, int64_t count)
+{
+    return count % 4 == 0 && countW % 4 == 0 && (((uintptr_t)ws | (uintptr_t)dW | (uintptr_t)db) & 15) == 0;
+}
+
 int launch_reduce_partials(const float *ws, float *dW, float *db, int64_t countW, int64_t count, int nsplit,
                            hipStream_t st)
 {
-    const bool vec = count % 4 == 0 && countW % 4 == 0 && ((uintptr_t)ws & 15) == 0 && ((uintptr_t)dW & 15) == 0 &&
-                     ((uintptr_t)db & 15) == 0;
-    if (vec) {
+    if (reduce_quads(ws, dW, db, countW, count)) {
         // A thread per quad where there are many quads with few loads each (256 -> 256 channels, 2 sets:
         // 8.6 us against 16 with sixteen groups), else as few groups as leave the chip full of blocks: a
         // wave then reads 1 KB runs.
@@ -107,6 +110,17 @@ int launch_reduce_partials(const float *ws, float *dW, float *db, int64_t countW
     }
     int64_t blocks = (count + 63) / 64;
     reduce_partials_kernel<<<dim3((unsigned)blocks), 256, 0, st>>>(ws, dW, db, countW, count, nsplit);
+    K3_LAUNCH_CHECK();
+    return K3_OK;
+}
+
+// The same with sixteen groups and two chains for any number of sets: the order of an fp32 sum then depends
+// on the number of sets alone (wgrad_ordered.hip), and on whether the alignment allows quads.
+int launch_reduce_ordered(const float *ws, float *dW, float *db, int64_t countW, int64_t count, int nsplit, hipStream_t st)
+{
+    if (!reduce_quads(ws, dW, db, countW, count)) return launch_reduce_partials(ws, dW, db, countW, count, nsplit, st);
+    reduce_partials_vec4_kernel<16, 8, 2><<<dim3((unsigned)((count / 4 + 15) / 16)), 256, 0, st>>>(
+        (const float4 *)ws, (float4 *)dW, (float4 *)db, countW / 4, count / 4, nsplit);
     K3_LAUNCH_CHECK();
     return K3_OK;
 }

@@ -37,7 +37,9 @@ int conv_fwd_general(const ConvArgs &a, hipStream_t st);
 int conv_dgrad_general(const ConvArgs &a, hipStream_t st);
 int conv_wgrad_general(const ConvArgs &a, float *dW, float *db, float *ws, hipStream_t st);
 size_t conv_wgrad_general_ws_bytes(int64_t N, int64_t D, int64_t H, int64_t W, int64_t cin, int64_t cout);
-int64_t conv_wgrad_general_sets(int64_t N, int64_t D, int64_t H, int64_t W, int64_t cin, int64_t cout);   // partial sums that holds
+int64_t conv_wgrad_general_sets(int64_t N, int64_t D, int64_t H, int64_t W);   // partial sums that holds
+int conv_wgrad_ordered(const ConvArgs &a, float *dW, float *db, float *ws, hipStream_t st);   // fp32 (wgrad_ordered.hip)
+int up_wgrad_ordered(const float *x, const float *dy, float *dW, float *db, float *ws, int64_t N, int D, int H, int W, int cin, int cout, hipStream_t st);
 
 // bf16 with channel counts in whole 16s that are no whole 32s, weights as they are (conv3d_narrow.hip);
 // the tensors on 16-byte boundaries
@@ -74,6 +76,7 @@ int launch_relu_bits(int dtype, const void *y, void *bits, int64_t nwords, hipSt
 // zeroes the elements of t whose bit is clear
 int launch_apply_relu_bits(int dtype, void *t, const void *bits, int64_t nwords, hipStream_t st);
 
+int launch_reduce_ordered(const float *ws, float *dW, float *db, int64_t countW, int64_t count, int nsplit, hipStream_t st);
 int launch_reduce_partials(const float *ws, float *dW, float *db, int64_t countW, int64_t count, int nsplit,
                            hipStream_t st);
 

@@ -15,19 +15,6 @@ namespace k3 {
 constexpr int HB = 256;       // voxels per batch
 constexpr int HEAD_K = 3;
 
-// n / d for 0 <= n < 2^31 by one 32 x 32 multiply: with 2^sh >= d the rounded-up 2^(32 + sh) / d - 2^32
-// is off by less than one part in 2^32, which cannot reach the next integer for such n.
-struct FastDiv {
-    unsigned d, m, sh;
-    static FastDiv of(unsigned d)
-    {
-        unsigned sh = 0;
-        while ((1ull << sh) < d) ++sh;
-        return {d, (unsigned)((((1ull << 32) * ((1ull << sh) - d)) / d) + 1), sh};
-    }
-    __device__ __forceinline__ unsigned quot(unsigned n) const { return (__umulhi(n, m) + n) >> sh; }
-};
-
 // a tensor and its up-sampling by 2 per axis: index of the small tensor's voxel under a large one's
 struct UpGeom {
     FastDiv w, h, d;   // sizes of the LARGE tensor

@@ -9,18 +9,25 @@
 
 namespace k3 {
 
-// General 3x3x3 kernel: the tap a lane group's slot of step s belongs to (S slots per voxel and chunk;
-// the last step may hold slots that belong to none, and a wave may look ahead past the last step).
-K3_HD int general_tap(int S, int s, int kg) { return S == 4 ? s : (4 * s + kg) / S; }
+// General 3x3x3 kernel.  Floats of a halo voxel in LDS: whole fours, and an odd number of them, so that
+// the 16 voxels of a block fall on different banks.
+K3_HD constexpr int general_pitch(int K) { return 4 * (((K + 3) / 4) | 1); }
 
-// Byte offset a wave adds to a step's weight loads, the same for all its lanes (S = 4: a step is one tap).
-// A wave that looks ahead past the last tap reads the last one again: a scalar offset is no part of
-// a descriptor's range check, so it has to lie inside the tensor by itself.
+// Element of the weights [27][cin][cout] that (tap, contraction channel k, row 0) is; K contraction channels,
+// M rows.  Forward contracts over cin, backward-data over cout.  The kernel adds this as a scalar offset,
+// which is no part of a descriptor's range check, so it has to lie inside the tensor by itself.
 template <typename I>
-K3_HD I general_weight_soff(int S, int s, bool bwd, I K, I M, int size)
+K3_HD I general_weight(bool bwd, int tap, int k, I K, I M) { return bwd ? (I)tap * M * K + k : ((I)tap * K + k) * M; }
+
+// The next place in the sum over (tap, channel): `step` channels on, KP in all (whole steps).  Behind the
+// last step it stays at the last tap, where a wave that looks ahead reads operands it does not use.
+K3_HD void general_next(int &tap, int &c, int step, int KP)
 {
-    const int tap = general_tap(S, s, 0) < 26 ? general_tap(S, s, 0) : 26;
-    return S == 4 ? (bwd ? 26 - tap : tap) * K * M * size : 0;
+    c += step;
+    if (c >= KP) {
+        c = 0;
+        tap = tap < 26 ? tap + 1 : 26;
+    }
 }
 
 // Offset of voxel (d, h, w) of a tile from the tile's first voxel.  I: 32 bits where a tile's span is

@@ -55,4 +55,24 @@ __device__ __forceinline__ f32x4 keep_positive(f32x4 v, f32x4 m)
     return v;
 }
 
+// A lane group kg of 16 lanes holds values 4 kg .. 4 kg + 3 of 16; afterwards v[j] holds value 4 j + kg: the
+// operands of four instructions in the order of the values (a 4 x 4 transposition over the lane groups).
+__device__ __forceinline__ void spread(float (&v)[4])
+{
+    auto swap32 = [](float &a, float &b) __attribute__((always_inline)) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    };
+    auto swap16 = [](float &a, float &b) __attribute__((always_inline)) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    };
+    swap32(v[0], v[2]);
+    swap32(v[1], v[3]);
+    swap16(v[0], v[1]);
+    swap16(v[2], v[3]);
+}
+
 }  // namespace k3

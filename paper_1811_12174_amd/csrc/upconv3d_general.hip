@@ -8,7 +8,8 @@
 // spread over many short workgroups.  The thread-per-output kernels these replace walked the
 // contraction with two loads per multiply-add.  Measured, before -> after (forward / backward-data /
 // backward-weight with its reduction): bf16 32 -> 16 at 2 x 20x24x28: 39 / 220 / 57 -> 10 / 10 / 16 us;
-// fp32 32 -> 16 at 24^3: 24 / 104 / 44 -> 7 / 6 / 16 us; fp32 64 -> 32 at 12^3: 21 / 62 / 57 -> 10 / 5 / 17 us.
+// fp32 32 -> 16 at 24^3: 25 / 106 / 44 -> 7 / 9 / 20 us; fp32 64 -> 32 at 12^3: 22 / 62 / 57 -> 8 / 14 / 21 us
+// (backward-weight of fp32: wgrad_ordered.hip).  Every sum keeps the order of the plain loop.
 #include "common.h"
 #include "conv_internal.h"
 #include "quad_io.h"
@@ -66,9 +67,10 @@ __device__ __forceinline__ void up_store(T *p, int c, int count, f32x4 v)
 }
 
 // Forward, D[output channel][voxel]: a workgroup takes 32 voxels x 16 output channels, each wave the two
-// taps of one row of the 2x2x2 block, so that its stores fill 2 neighbouring voxels.  A lane group of
-// 16 carries 4 channels of the contraction through four matrix instructions (the order of the sum is
-// permuted alike on both sides).
+// taps of one row of the 2x2x2 block, so that its stores fill 2 neighbouring voxels.  An instruction
+// multiplies four neighbouring channels, lane group kg carrying channel kg of them, and the accumulators
+// start from the bias: the sums are those of the plain loop over the channels (see
+// conv_general_kernel for why that order is kept).
 template <typename T, bool QUAD>
 __global__ __launch_bounds__(256) void up_general_fwd_kernel(UpGeneral<T> p)
 {
@@ -87,25 +89,34 @@ __global__ __launch_bounds__(256) void up_general_fwd_kernel(UpGeneral<T> p)
         in[b] = v < p.V;
         xp[b] = p.x + (in[b] ? v : 0) * p.cin;
     }
+    const int m = co0 + kg * 4;
     f32x4 acc[2][2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int r = 0; r < 4; ++r) {
+        const float bias = p.bias && m + r < p.cout ? p.bias[m + r] : 0.f;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[t][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto fetch = [&](int c, f32x4 (&x)[2], float (&a)[2][4]) __attribute__((always_inline)) {
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) x[b] = up_quad<T, QUAD>(xp[b], c + kg * 4, p.cin, in[b]);
+            for (int b = 0; b < 2; ++b) acc[t][b][r] = bias;
+    }
+    auto fetch = [&](int c, float (&x)[2][4], float (&a)[2][4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {         // (dealt out by spread() before they are used)
+            const f32x4 v = up_quad<T, QUAD>(xp[b], c + kg * 4, p.cin, in[b]);
+            x[b][0] = v[0]; x[b][1] = v[1]; x[b][2] = v[2]; x[b][3] = v[3];
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int ci = c + kg * 4 + j;
-            const bool ok = row && ci < p.cin;
+            const int ci = c + j * 4 + kg;
+            const bool ok = ci < p.cin;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) a[t][j] = ok ? elem<T>::ld(w + ((int64_t)t * p.cin + ci) * p.cout) : 0.f;
+            for (int t = 0; t < 2; ++t) a[t][j] = ok && row ? elem<T>::ld(w + ((int64_t)t * p.cin + ci) * p.cout) : 0.f;
         }
     };
-    f32x4 x[2][2];
-    float a[2][2][4];
-    auto multiply = [&](f32x4 (&xs)[2], float (&as)[2][4]) __attribute__((always_inline)) {
+    float x[2][2][4], a[2][2][4];
+    auto multiply = [&](float (&xs)[2][4], float (&as)[2][4]) __attribute__((always_inline)) {
+        spread(xs[0]);
+        spread(xs[1]);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -121,78 +132,84 @@ __global__ __launch_bounds__(256) void up_general_fwd_kernel(UpGeneral<T> p)
         if (c + 32 < p.cin) fetch(c + 32, x[0], a[0]);
         multiply(x[1], a[1]);
     }
-    f32x4 bias = {0.f, 0.f, 0.f, 0.f};
-    const int m = co0 + kg * 4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (p.bias && m + r < p.cout) bias[r] = p.bias[m + r];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         if (!in[b]) continue;
         T *out = p.y + (up_origin(p, v0 + b * 16 + ln) + up_tap(p, 2 * wv)) * p.cout;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) up_store<T, QUAD>(out + t * p.cout, m, p.cout, acc[t][b] + bias);
+        for (int t = 0; t < 2; ++t) up_store<T, QUAD>(out + t * p.cout, m, p.cout, acc[t][b]);
     }
 }
 
-// Backward-data, D[input channel][voxel]: a workgroup takes 32 voxels x 16 input channels; its waves split
-// the contraction over (tap, output channel) by rows of the 2x2x2 block and add their sums through
-// LDS in a fixed order.
+// Backward-data, D[input channel][voxel]: a wave takes 32 voxels x 16 input channels and walks the whole
+// contraction, tap after tap and the output channels of a tap in order (as above), the four waves of a
+// workgroup four groups of voxels.
 template <typename T, bool QUAD>
 __global__ __launch_bounds__(256) void up_general_dgrad_kernel(UpGeneral<T> p)
 {
-    __shared__ __attribute__((aligned(16))) float red[4 * 2 * 64 * 4];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kg = lane >> 4, ln = lane & 15;
     const int ci0 = (int)(blockIdx.x % (unsigned)p.nblk) * 16;
-    const int64_t v0 = (int64_t)(blockIdx.x / (unsigned)p.nblk) * 32;
+    const int64_t v0 = ((int64_t)(blockIdx.x / (unsigned)p.nblk) * 4 + wv) * 32;
+    if (v0 >= p.V) return;
     const int ci = ci0 + ln;
     const bool row = ci < p.cin;
-    const T *w = p.w + ((int64_t)(2 * wv) * p.cin + (row ? ci : 0)) * p.cout;
-    const int64_t wt = (int64_t)p.cin * p.cout;
+    const T *w = p.w + (int64_t)(row ? ci : 0) * p.cout;
     const T *gp[2];
     bool in[2];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         const int64_t v = v0 + b * 16 + ln;
         in[b] = v < p.V;
-        gp[b] = p.dy + (in[b] ? (up_origin(p, v) + up_tap(p, 2 * wv)) * p.cout : 0);
+        gp[b] = p.dy + (in[b] ? up_origin(p, v) * p.cout : 0);
     }
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    auto fetch = [&](int c, f32x4 (&g)[2][2], f32x4 (&a)[2]) __attribute__((always_inline)) {
+    // a step: 16 output channels of one tap; the next one's operands are on their way
+    auto fetch = [&](int t, int c, float (&g)[2][4], float (&a)[4]) __attribute__((always_inline)) {
+        const int64_t go = up_tap(p, t) * p.cout;
+        const f32x4 v = up_quad<T, QUAD>(w + (int64_t)t * p.cin * p.cout, c + kg * 4, p.cout, row);
+        a[0] = v[0]; a[1] = v[1]; a[2] = v[2]; a[3] = v[3];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            a[t] = up_quad<T, QUAD>(w + t * wt, c + kg * 4, p.cout, row);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) g[t][b] = up_quad<T, QUAD>(gp[b] + t * p.cout, c + kg * 4, p.cout, in[b]);
+        for (int b = 0; b < 2; ++b) {
+            const f32x4 u = up_quad<T, QUAD>(gp[b] + go, c + kg * 4, p.cout, in[b]);
+            g[b][0] = u[0]; g[b][1] = u[1]; g[b][2] = u[2]; g[b][3] = u[3];
         }
     };
-    auto multiply = [&](f32x4 (&g)[2][2], f32x4 (&a)[2]) __attribute__((always_inline)) {
+    auto multiply = [&](float (&g)[2][4], float (&a)[4]) __attribute__((always_inline)) {
+        spread(a);
+        spread(g[0]);
+        spread(g[1]);
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[b] = mfma_f32(a[t][j], g[t][b][j], acc[b]);
+            for (int b = 0; b < 2; ++b) acc[b] = mfma_f32(a[j], g[b][j], acc[b]);
     };
-    f32x4 g[2][2][2], a[2][2];
-    fetch(0, g[0], a[0]);
-    for (int c = 0; c < p.cout; c += 32) {
-        if (c + 16 < p.cout) fetch(c + 16, g[1], a[1]);
+    const int per = (p.cout + 15) / 16, steps = 8 * per;     // an even number
+    int t = 0, c = 0;
+    auto advance = [&]() __attribute__((always_inline)) {
+        c += 16;
+        if (c >= p.cout) {
+            c = 0;
+            t = t < 7 ? t + 1 : 7;                            // behind the last step: read again, not used
+        }
+    };
+    float g[2][2][4], a[2][4];
+    fetch(t, c, g[0], a[0]);
+    advance();
+    for (int s = 0; s < steps; s += 2) {                      // the register sets have fixed names
+        fetch(t, c, g[1], a[1]);
+        advance();
         multiply(g[0], a[0]);
-        if (c + 16 >= p.cout) break;
-        if (c + 32 < p.cout) fetch(c + 32, g[0], a[0]);
+        fetch(t, c, g[0], a[0]);
+        advance();
         multiply(g[1], a[1]);
     }
+    const int m = ci0 + kg * 4;
 #pragma unroll
-    for (int b = 0; b < 2; ++b) *reinterpret_cast<f32x4 *>(red + ((wv * 2 + b) * 64 + lane) * 4) = acc[b];
-    __syncthreads();
-    const int64_t v = v0 + wv * 16 + ln;
-    if (wv < 2 && v < p.V) {
-        f32x4 s = *reinterpret_cast<const f32x4 *>(red + (wv * 64 + lane) * 4);
-#pragma unroll
-        for (int k = 1; k < 4; ++k) s += *reinterpret_cast<const f32x4 *>(red + ((k * 2 + wv) * 64 + lane) * 4);
-        const int m = ci0 + kg * 4;
+    for (int b = 0; b < 2; ++b) {
+        if (!in[b]) continue;
+        const int64_t v = v0 + b * 16 + ln;
+        f32x4 s = acc[b];
         if (p.mask) s = keep_positive(s, up_quad<T, QUAD>(p.mask + v * p.cin, m, p.cin, true));
         up_store<T, QUAD>(p.dx + v * p.cin, m, p.cin, s);
     }
@@ -305,7 +322,7 @@ static int up_dgrad_t(const void *dy, const void *w, void *dx, const void *mask,
     UpGeneral<T> p = up_general_args<T>(N, D, H, W, cin, cout);
     p.dy = (const T *)dy; p.w = (const T *)w; p.mask = (const T *)mask; p.dx = (T *)dx;
     p.nblk = (cin + 15) / 16;
-    const int64_t blocks = (p.V + 31) / 32 * p.nblk;
+    const int64_t blocks = (p.V + 127) / 128 * p.nblk;
     if (blocks > 0x7fffffffLL) return K3_E_UNSUPPORTED;
     const bool quad = cin % 4 == 0 && cout % 4 == 0 && quad_aligned<T>(dy) && quad_aligned<T>(w) && quad_aligned<T>(dx) && quad_aligned<T>(mask);
     if (quad) up_general_dgrad_kernel<T, true><<<dim3((unsigned)blocks), 256, 0, st>>>(p);
@@ -350,7 +367,7 @@ static int up_wgrad_t(const void *x, const void *dy, float *dW, float *db, float
 int up_general_wgrad(int dtype, const void *x, const void *dy, float *dW, float *db, float *ws, int64_t max_sets, int64_t N, int D, int H,
                      int W, int cin, int cout, hipStream_t st)
 {
-    return dtype == K3_F32 ? up_wgrad_t<float>(x, dy, dW, db, ws, max_sets, N, D, H, W, cin, cout, st)
+    return dtype == K3_F32 ? up_wgrad_ordered((const float *)x, (const float *)dy, dW, db, ws, N, D, H, W, cin, cout, st)
                            : up_wgrad_t<bf16_t>(x, dy, dW, db, ws, max_sets, N, D, H, W, cin, cout, st);
 }
 

@@ -1,7 +1,7 @@
 """The general 3x3x3 kernels (fp32, and bf16 with odd channel counts) against the fp64 oracle at the
-sizes where their dispatch and their tiles change: 4 / 8 / 16-channel contraction slots and one more
-than each, 128-voxel tiles with one and two output blocks, 32-voxel tiles with the contraction split
-over the waves, edges one short of and one past a tile, channel quads and widths that are none."""
+sizes where their dispatch and their tiles change: 4, 8 and 16 contraction channels and one more
+than each, 128-voxel tiles with one and two output blocks, the smaller tiles, edges one short of and
+one past a tile, channel quads and widths that are none."""
 import numpy as np
 import pytest
 
@@ -12,15 +12,15 @@ pytestmark = pytest.mark.gpu
 # (N, D, H, W, c1, c2, cout, dtype)
 CASES = [
     (1, 1, 1, 1, 1, 0, 1, "f32"),          # one voxel
-    (1, 2, 4, 4, 4, 0, 16, "f32"),         # exactly one 32-voxel tile, one slot per voxel
-    (1, 3, 5, 5, 8, 0, 17, "f32"),         # one past a tile on every axis, two slots, one row past a block
+    (1, 2, 4, 4, 4, 0, 16, "f32"),         # exactly one 32-voxel tile, one quad per voxel
+    (1, 3, 5, 5, 8, 0, 17, "f32"),         # one past a tile on every axis, two quads, one row past a block
     (1, 4, 7, 9, 5, 0, 8, "f32"),          # channels that are no quad
-    (1, 5, 6, 7, 4, 4, 12, "f32"),         # one 8-channel chunk that straddles two sources
-    (1, 6, 5, 7, 12, 8, 20, "f32"),        # a 16-channel chunk that straddles two sources, and a partial one
+    (1, 5, 6, 7, 4, 4, 12, "f32"),         # two sources in 8 channels
+    (1, 6, 5, 7, 12, 8, 20, "f32"),        # two sources in 16 staged channels, and a partial step
     (1, 28, 29, 33, 16, 0, 16, "f32"),     # 280 128-voxel tiles, one output block, one past a tile
-    (1, 28, 28, 31, 16, 16, 32, "f32"),    # 196 tiles: split contraction, 16-channel blocks, two sources
+    (1, 28, 28, 31, 16, 16, 32, "f32"),    # 196 tiles: smaller ones, two sources
     (2, 24, 28, 40, 20, 0, 36, "f32"),     # 128-voxel tiles with two output blocks, the second one partial
-    (1, 33, 28, 39, 4, 0, 40, "f32"),      # the same at one slot per voxel
+    (1, 33, 28, 39, 4, 0, 40, "f32"),      # the same at one quad per voxel
     (1, 12, 11, 10, 40, 0, 24, "bf16"),    # bf16, quads
     (1, 30, 31, 34, 6, 0, 20, "bf16"),     # bf16, no quads, 128-voxel tiles
 ]
@@ -134,8 +134,8 @@ def test_weight_gradient_of_more_blocks_than_a_grid_axis_has():
     assert torch.equal(dW, want) and torch.equal(db, g0 + g1)
 
 
-@pytest.mark.parametrize("ch", [1, 4, 5, 8])      # one and two slots a voxel, with and without quads
-@pytest.mark.parametrize("size", [(4, 4, 8), (33, 28, 39)])      # split contraction, 128-voxel tiles
+@pytest.mark.parametrize("ch", [1, 4, 5, 8])      # one and two quads a voxel, whole and partial
+@pytest.mark.parametrize("size", [(4, 4, 8), (33, 28, 39)])      # small and 128-voxel tiles
 def test_an_infinite_input_stays_infinite(orc, ch, size):
     import torch
     from paper_1811_12174_amd import k3

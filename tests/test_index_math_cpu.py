@@ -11,7 +11,10 @@ SRC = r"""
 #include "index_math.h"
 using namespace k3;
 extern "C" {
-int64_t weight_soff(int S, int s, int bwd, int64_t K, int64_t M, int size) { return general_weight_soff<int64_t>(S, s, bwd, K, M, size); }
+int64_t weight(int bwd, int tap, int k, int64_t K, int64_t M) { return general_weight<int64_t>(bwd, tap, k, K, M); }
+int next_tap(int tap, int c, int step, int K) { general_next(tap, c, step, K); return tap; }
+int next_c(int c, int step, int K) { int tap = 0; general_next(tap, c, step, K); return c; }
+int pitch(int K) { return general_pitch(K); }
 int64_t block(int b, int nkc) { return packed_block(b, nkc); }
 int64_t step(int tap, int nkc, int kc) { return packed_step(tap, nkc, kc); }
 int fit(int64_t K) { return small_weights_fit(K); }
@@ -33,7 +36,10 @@ def lib(tmp_path_factory):
                            "-I" + os.path.join(ROOT, "paper_1811_12174_amd", "csrc"), "-o", so, cpp])
     L = ctypes.CDLL(so)
     q, i = ctypes.c_int64, ctypes.c_int
-    L.weight_soff.restype, L.weight_soff.argtypes = q, [i, i, i, q, q, i]
+    L.weight.restype, L.weight.argtypes = q, [i, i, i, q, q]
+    L.next_tap.restype, L.next_tap.argtypes = i, [i, i, i, i]
+    L.next_c.restype, L.next_c.argtypes = i, [i, i, i]
+    L.pitch.restype, L.pitch.argtypes = i, [i]
     L.block.restype, L.block.argtypes = q, [i, i]
     L.step.restype, L.step.argtypes = q, [i, i, i]
     L.fit.restype, L.fit.argtypes = i, [q]
@@ -44,20 +50,34 @@ def lib(tmp_path_factory):
     return L
 
 
-@pytest.mark.parametrize("S", [1, 2, 4])
-@pytest.mark.parametrize("wk", [1, 4])       # waves that split the steps
+@pytest.mark.parametrize("U", [1, 4])            # instructions of four channels a step
 @pytest.mark.parametrize("bwd", [0, 1])
-def test_general_kernel_asks_for_no_weights_outside_the_tensor(lib, S, wk, bwd):
-    K, M, size = 40, 24, 4
-    nstep, ahead = (27 * S + 3) // 4, 2
-    mysteps = (nstep + wk - 1) // wk
-    for w in range(wk):
-        for i in range(mysteps + ahead):
-            if i >= ahead and i >= mysteps:      # the kernel looks ahead only while its own steps last
-                continue
-            off = lib.weight_soff(S, i * wk + w, bwd, K, M, size)
-            # the lanes add up to one tap's K x M
-            assert 0 <= off and off + K * M * size <= 27 * K * M * size, (S, wk, w, i)
+def test_general_kernel_asks_for_no_weights_outside_the_tensor(lib, U, bwd):
+    M = 24
+    for K in (4, 16, 20, 48) if U == 1 else (16, 48):
+        for tap in range(27):
+            for c in range(0, K, 4):
+                base = lib.weight(bwd, tap, c, K, M)
+                for m in (0, M - 1):
+                    for kg in range(4):
+                        at = base + (m * K + kg if bwd else kg * M + m)
+                        assert at == ((tap * M + m) * K + c + kg if bwd else (tap * K + c + kg) * M + m)
+                        assert 0 <= base <= at < 27 * K * M
+        # (tap, c) as the kernel steps through them, two or eight steps ahead: behind the last tap it stays there
+        tap, c = 0, 0
+        for _ in range(27 * K // (4 * U) + 9):
+            assert 0 <= lib.weight(bwd, tap, c + 4 * (U - 1), K, M) <= 27 * K * M - (4 if bwd else 4 * M)
+            tap, c = lib.next_tap(tap, c, 4 * U, K), lib.next_c(c, 4 * U, K)
+            assert tap <= 26
+
+
+@pytest.mark.parametrize("K", [1, 3, 4, 5, 8, 16, 20, 64, 128, 256, 400])
+def test_halo_voxels_lie_on_different_banks(lib, K):
+    pitch = lib.pitch(K)
+    assert pitch >= K and pitch % 4 == 0
+    for kg in range(4):      # 16 neighbouring voxels, one word each, and the four channels of an instruction
+        assert len({(v * pitch + kg) % 64 for v in range(16)}) == 16
+    assert len({(v * pitch + kg) % 64 for v in range(16) for kg in range(4)}) == 64
 
 
 def test_offsets_inside_a_tile_of_wide_planes(lib):
