@@ -1465,9 +1465,10 @@ static int mfma_variant(const MfmaParams &p, int64_t mblocks)
     // ... and the halo tile's voxel offsets in 24 bits, its byte offsets in 31 (the copies' offset arithmetic)
     const bool fits = (int64_t)10 * p.H * p.W * (cmax > 1 ? cmax : 1) < 0x7fffffffLL && p.cd1 + p.cd2 <= 1024 &&
                       (int64_t)11 * p.H * p.W < (1 << 24) && (int64_t)11 * p.H * p.W * smax * 2 < 0x7fffffffLL;
-    // Up to 512 workgroups of 64 voxels x 32 channels: the small-volume kernel (16^3 256->256, 512 of them:
-    // 22 us against 27 on the pipelined kernel, 4^3 128->128: 8.5 against 13.7 -- 59.8 on the first one;
-    // 32^3 64->64, 1024: 18 against 11)
+    // Up to 512 workgroups of 64 voxels x 32 channels, one wave per SIMD: the small-volume kernel (16^3
+    // 256->256, 512 of them: 23.1 us against 26.5 on the pipelined kernel, 32^3 32->32: 7.1 against 8.6;
+    // 4^3 128->128: 10.2 against 59.6 on the first one; beyond, 24^3 96->96, 648: 20.8 against 13.0,
+    // 32^3 64->64, 1024: 18.0 against 11.4)
     const int64_t cubes = (int64_t)p.N * ((p.D + 3) / 4) * ((p.H + 3) / 4) * ((p.W + 3) / 4);
     if (fits && cubes * mblocks <= 512 && small_weights_fit(p.c1 + p.c2)) return 5;
     if (!p.mask && fits) {

@@ -1,6 +1,6 @@
 """The small-volume bf16 kernel (forward and backward-data) against the fp64 oracle where it can go
 wrong: one voxel, one 4x4x4 tile and one voxel more on every axis, one and several 32-channel chunks,
-one and two 16-channel output blocks per workgroup, two sources and destinations, input masks, output
+one and several output blocks, more channels than LDS holds at a time, two sources and destinations, input masks, output
 masks as tensor and as bits; and the masked first kernel just past the small kernel's range."""
 import numpy as np
 import pytest
@@ -16,9 +16,9 @@ CASES = [
     (1, 5, 5, 5, 32, 0, 64),          # one past a tile on every axis
     (2, 3, 7, 6, 96, 0, 32),          # three chunks
     (1, 4, 5, 3, 32, 64, 96),         # sources of unequal width, three output blocks of 32
-    (1, 16, 16, 16, 64, 0, 64),       # 256 workgroups of one output block: the last with one
-    (1, 16, 16, 17, 64, 0, 64),       # the first with two
-    (1, 16, 16, 32, 128, 128, 128),   # 512 workgroups of two: the last of the range
+    (1, 16, 16, 16, 64, 0, 64),
+    (1, 16, 16, 17, 64, 0, 64),
+    (1, 16, 16, 32, 128, 128, 128),   # 512 workgroups forward: the last of the range; two loads of 128 channels
     (2, 20, 24, 24, 64, 0, 64),       # past the range: pipelined kernels, and the first kernel for masked inputs
 ]
 

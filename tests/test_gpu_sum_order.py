@@ -1,4 +1,5 @@
-"""The general kernels (fp32, and bf16 with odd channel counts) sum in the order of the definition: bias,
+"""The bf16 kernel of small volumes sums in the order of those of larger ones (last test here).
+The general kernels (fp32, and bf16 with odd channel counts) sum in the order of the definition: bias,
 then tap after tap, the channels of a tap in order, one fused multiply-add per term; the fp32 weight
 gradients in sets, chains and groups that depend on the sizes alone.  All passes of the 3x3x3 and the
 transposed convolution are held to those loops bit for bit, at sizes that reach every tile and form of
@@ -253,3 +254,51 @@ def test_weight_gradient_of_the_transposed_convolution(loops, case):
     wantW, wantb = np.empty((2, 2, 2, ci, co), np.float32), np.empty((co,), np.float32)
     run(loops.wgrad, np.ascontiguousarray(x, dtype=np.float32), np.ascontiguousarray(g, dtype=np.float32), wantW, wantb, *sp, ci, co, (8,))
     assert same(dW, wantW, "f32") and same(db, wantb, "f32")
+
+
+# (D, H, W), c1, c2, cout
+SMALL = [
+    ((1, 2, 3), 32, 0, 32),
+    ((4, 4, 4), 128, 0, 128),
+    ((5, 6, 9), 32, 96, 64),
+    ((8, 8, 8), 256, 0, 64),
+    ((16, 16, 16), 32, 0, 128),     # 64 tiles of 4x8x8 voxels x 32 channels: sums start from the bias
+]
+
+
+@pytest.mark.parametrize("case", SMALL, ids=lambda c: "x".join(map(str, c)))
+def test_bf16_sums_do_not_depend_on_the_batch(case):
+    """A sample alone goes to the small-volume kernel, as one of many to the kernels of larger volumes;
+    all of them add in the same order, so the sample's results are the same to the bit.  Fewer than
+    48 tiles add the bias at the end, as the first matrix kernel does: there the bias is zero."""
+    import torch
+    from paper_1811_12174_amd import k3
+    from gpu_util import to_dev, empty, packed_for
+    (D, H, W), c1, c2, co = case
+    sp, cin = (D, H, W), c1 + c2
+    cubes = -(-D // 4) * -(-H // 4) * -(-W // 4)
+    small = -(-D // 4) * -(-H // 8) * -(-W // 8)
+    many = 512 // (cubes * min(cin, co) // 32) + 1
+    assert cubes * max(cin, co) // 32 <= 512 < many * cubes * min(cin, co) // 32
+    x = to_dev(synth.activations(700, (1,) + sp + (cin,), "bf16"), "bf16")
+    w = to_dev(synth.conv_weights(701, cin, co, "bf16"), "bf16")
+    dy, ym = (to_dev(synth.activations(s, (1,) + sp + (co,), "bf16"), "bf16") for s in (702, 703))
+    b = torch.from_numpy(synth.normal(synth.SEED, 704, (co,), np.float32)).cuda()
+    if small * co // 32 < 48:
+        b.zero_()
+    pk = packed_for(w)
+
+    def run_all(n):
+        rep = lambda t: t.expand((n,) + t.shape[1:]).contiguous()
+        y = empty((n,) + sp + (co,), "bf16")
+        k3.conv3d_fwd(rep(x[..., :c1]), w, pk, b, 0, y, x2=rep(x[..., c1:]) if c2 else None)
+        out = [y[-1]]
+        for mask in (None, rep(ym)):
+            dx = empty((n,) + sp + (c1,), "bf16")
+            dx2 = empty((n,) + sp + (c2,), "bf16") if c2 else None
+            k3.conv3d_bwd_data(rep(dy), mask, w, pk, dx, dx2=dx2)
+            out += [dx[-1]] + ([dx2[-1]] if c2 else [])
+        torch.cuda.synchronize()
+        return out
+    for one, of_many in zip(run_all(1), run_all(many)):
+        assert torch.equal(one, of_many)
