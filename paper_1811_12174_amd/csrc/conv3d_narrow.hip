@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, MB == 1 ? 4 : 3) void conv_narrow_kernel(Narro
             if (p.mask) {                     // backward-data: one source
                 const u32v4 m = __builtin_amdgcn_raw_buffer_load_b128(rm, vo[k] < 0 ? -1 : (vo[k] * p.c1 + ch) * 2, 0, 0);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) sx[k][j] = mask_pair(sx[k][j], m[j]);
+                for (int j = 0; j < 4; ++j) sx[k][j] = mask_pair_to(sx[k][j], m[j], MASK_NUMBERS);
             }
         }
     };
@@ -172,6 +172,7 @@ __global__ __launch_bounds__(256, MB == 1 ? 4 : 3) void conv_narrow_kernel(Narro
 // workgroup takes every nsplit-th tile, the next one's loads in flight, and writes one set of partial sums.
 struct NarrowWgrad {
     const bf16_t *x1, *x2, *g, *mask;
+    unsigned mask_top;        // MASK_NUMBERS; in place of the kernel for whole 32s MASK_SIGN, as there
     int c1, c2, cout;
     float *outW, *outB;       // first set of partial sums and its bias part, or the gradients themselves (outB may be null)
     int64_t per_split;
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(256, 3) void conv_narrow_wgrad_kernel(NarrowWgrad p
             if (p.mask) {
                 const u32v4 m = __builtin_amdgcn_raw_buffer_load_b128(rm, o, 0, 0);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) sg[k][j] = mask_pair(sg[k][j], m[j]);
+                for (int j = 0; j < 4; ++j) sg[k][j] = mask_pair_to(sg[k][j], m[j], p.mask_top);
             }
         }
     };
@@ -382,7 +383,7 @@ __global__ __launch_bounds__(256) void conv_first16_wgrad_kernel(NarrowWgrad p)
                 if (p.mask) {
                     const u32v4 m = *reinterpret_cast<const u32v4 *>(p.mask + o);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) sg[k][j] = mask_pair(sg[k][j], m[j]);
+                    for (int j = 0; j < 4; ++j) sg[k][j] = mask_pair_to(sg[k][j], m[j], MASK_NUMBERS);
                 }
             }
         }
@@ -548,6 +549,7 @@ int conv_wgrad_narrow(const ConvArgs &a, float *dW, float *db, float *ws, int64_
     if (tiles > 0x7fffffffLL || nsplit * blocks > 0x7fffffffLL) return K3_E_UNSUPPORTED;
     p.x1 = (const bf16_t *)a.x; p.x2 = (const bf16_t *)a.x2;
     p.g = (const bf16_t *)a.dy; p.mask = (const bf16_t *)a.ymask;
+    p.mask_top = mfma_ok(K3_BF16, a.c1, a.c2, a.cout) ? MASK_SIGN : MASK_NUMBERS;
     p.c1 = (int)a.c1; p.c2 = (int)a.c2; p.cout = (int)a.cout;
     p.per_split = 27 * cin * a.cout + a.cout;
     p.outW = nsplit > 1 ? ws : dW;

@@ -161,7 +161,13 @@ __global__ __launch_bounds__(128, 1) void conv_small_kernel(MfmaParams p, int bi
     uint4 *dst = reinterpret_cast<uint4 *>((d1 ? p.dst1 : p.dst2) + eo);
     dst[0] = make_uint4(o[0], o[1], o[2], o[3]);
     dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
-    if (p.bits_out) p.bits_out[vox * (p.cd1 / 16) + co / 16] = (unsigned short)relu_bits16(o);      // (forward: one destination)
+    if (p.bits_out) {                                      // (forward: one destination)
+        if (bias_last) {                                   // in place of the first kernel, whose bits a pass of their own wrote
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[i] = mask_pair_to(o[i], o[i], MASK_NUMBERS);
+        }
+        p.bits_out[vox * (p.cd1 / 16) + co / 16] = (unsigned short)relu_bits16(o);
+    }
 }
 
 int launch_conv_small(MfmaParams p, hipStream_t st)

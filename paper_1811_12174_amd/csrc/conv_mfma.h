@@ -35,6 +35,16 @@ __device__ __forceinline__ uint32_t mask_pair(uint32_t v, uint32_t m)
     return v & (lo | hi);
 }
 
+// The same with the bf16 values 1 .. top of m, as integers, counting as positive: MASK_NUMBERS keeps only what
+// compares > 0, MASK_SIGN also a NaN whose sign is clear, like mask_pair.
+constexpr unsigned MASK_NUMBERS = 0x7f80u, MASK_SIGN = 0x7fffu;
+__device__ __forceinline__ uint32_t mask_pair_to(uint32_t v, uint32_t m, unsigned top)
+{
+    const uint32_t lo = (m & 0xffffu) - 1u < top ? 0x0000ffffu : 0u;
+    const uint32_t hi = (m >> 16) - 1u < top ? 0xffff0000u : 0u;
+    return v & (lo | hi);
+}
+
 typedef __attribute__((ext_vector_type(4))) unsigned u32v4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32v2;
 
@@ -53,8 +63,8 @@ __device__ __forceinline__ void store_block16(const MfmaParams &p, f32x4 s, bool
     const int64_t eo = d1 ? vox * p.cd1 + m : vox * p.cd2 + (m - p.cd1);
     if (in && d1 && p.omask) {
         const u32v2 k = *reinterpret_cast<const u32v2 *>(p.omask + eo);
-        o[0] = mask_pair(o[0], k[0]);
-        o[1] = mask_pair(o[1], k[1]);
+        o[0] = mask_pair_to(o[0], k[0], MASK_NUMBERS);
+        o[1] = mask_pair_to(o[1], k[1], MASK_NUMBERS);
     }
     if (in && d1 && p.omask_bits) {
         const unsigned k = p.omask_bits[vox * (p.cd1 / 16) + mblk / 16] >> (kg * 4);
@@ -63,7 +73,7 @@ __device__ __forceinline__ void store_block16(const MfmaParams &p, f32x4 s, bool
     }
     if (in) *reinterpret_cast<u32v2 *>((d1 ? p.dst1 : p.dst2) + eo) = o;
     if (p.bits_out) {   // (forward: one destination) the four lane groups hold four bits each of the voxel's word
-        const unsigned z0 = bf16_pair_positive(o[0]), z1 = bf16_pair_positive(o[1]);
+        const unsigned z0 = mask_pair_to(0x00010001u, o[0], MASK_NUMBERS), z1 = mask_pair_to(0x00010001u, o[1], MASK_NUMBERS);
         unsigned z = (z0 & 1u) | ((z0 >> 15) & 2u) | ((z1 & 1u) << 2) | ((z1 >> 13) & 8u);
         z <<= kg * 4;
         z |= __shfl_xor(z, 16);

@@ -121,3 +121,52 @@ def test_weight_gradient_of_small_volumes(orc, case, masked):
     assert rel_l2(to_f64(dW), rW) < 1e-5
     assert rel_l2(to_f64(db), rb) < 1e-5
     assert torch.equal(dW, dW2)
+
+
+@pytest.mark.parametrize("case", [((1, 5, 6, 9), 16, 16), ((1, 3, 5, 17), 1, 16), ((1, 4, 4, 4), 32, 32)],
+                         ids=["16-16", "1-16", "32-32"])
+def test_a_mask_that_is_not_a_number_is_not_positive(case):
+    """Masks are > 0 as values: +NaN and -NaN count like zero (weight gradients of channels in whole 32s
+    go by the sign instead: there +NaN counts like one), +Inf like any positive number."""
+    import torch
+    from paper_1811_12174_amd import k3
+    from gpu_util import to_dev, empty, packed_for
+    sp, ci, co = case
+    x, dy = (to_dev(synth.activations(s, sp + (c,), "bf16"), "bf16") for s, c in ((730, ci), (731, co)))
+    w = to_dev(synth.conv_weights(732, ci, co, "bf16"), "bf16")
+    pk = packed_for(w)
+    odd = torch.tensor([0x7fc0, 0x7f81, -64, -127, 0x7f80, -128, 0, -0x8000, 0x3f80], dtype=torch.int32)   # NaNs, infinities, zeros, one
+
+    def masks(c, seed):
+        m = synth.activations(seed, sp + (c,), "bf16")
+        m = to_dev(m, "bf16").cpu().view(torch.int16)
+        pick = torch.arange(m.numel()) % 3 == 0
+        m.view(-1)[pick] = odd.to(torch.int16).repeat(m.numel() // 27 + 1)[:int(pick.sum())]
+        m = m.view(torch.bfloat16)
+        zero, one = m.clone(), m.clone()
+        zero[m.isnan()] = 0
+        one[m.isnan() & (m.view(torch.int16) > 0)] = 1
+        return m.cuda(), zero.cuda(), one.cuda()
+    ym, ym0, ym1 = masks(co, 733)
+    om, om0, _ = masks(ci, 734)
+
+    def wgrad(mask):
+        ws = torch.empty(k3.conv3d_bwd_weight_workspace_bytes(x, dy), device="cuda", dtype=torch.uint8)
+        dW, db = torch.empty((3, 3, 3, ci, co), device="cuda"), torch.empty(co, device="cuda")
+        k3.conv3d_bwd_weight(x, dy, mask, dW, db, ws)
+        return torch.cat([dW.flatten(), db])
+    assert torch.equal(wgrad(ym), wgrad(ym1 if ci % 32 == 0 else ym0))
+    if ci == 16:
+        def dgrad(mask, omask):
+            dx = empty(sp + (ci,), "bf16")
+            k3.conv3d_bwd_data(dy, mask, w, pk, dx, dx_mask=omask)
+            return dx
+        assert torch.equal(dgrad(ym, om), dgrad(ym0, om0))
+    # bits of an output that holds NaN (no ReLU): of channels whose bias is one
+    b = torch.zeros(co, device="cuda")
+    b[::5] = float("nan")
+    y = empty(sp + (co,), "bf16")
+    bits = torch.empty(k3.relu_bits_bytes(y) // 2, device="cuda", dtype=torch.int16)
+    k3.conv3d_fwd_bits(x, w, pk, b, 0, y, bits)
+    words = (y.float().cpu().numpy().reshape(-1, 16) > 0).astype(np.uint32) @ (1 << np.arange(16, dtype=np.uint32))
+    assert bool(y.isnan().any()) and np.array_equal(bits.cpu().numpy().view(np.uint16), words.astype(np.uint16))
