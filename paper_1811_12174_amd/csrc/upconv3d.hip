@@ -8,7 +8,8 @@
 // consecutive channels) and the activations the B operand, read straight from global
 // memory: a lane needs 8 consecutive channels of one voxel, which is a 16-byte load.
 // Backward-weight contracts over voxels and uses transposing LDS reads like the 3x3x3
-// weight-gradient kernel.  Other dtypes / channel counts use direct kernels.
+// weight-gradient kernel.  Other dtypes / channel counts, and backward-weight of bf16 levels of few
+// voxels, go to upconv3d_general.hip.
 #include "common.h"
 #include "conv_internal.h"
 #include "conv_mfma.h"

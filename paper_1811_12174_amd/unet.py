@@ -303,6 +303,9 @@ class StepNet:
         memory of the step: its tensors then live in one slab of budget minus the fixed part (see
         fixed_bytes), and device copies of swapped tensors are dropped only when an allocation finds
         no room, oldest first.
+        A step under a plan whose tensors are less than 1 GiB together waits, before it starts, until
+        the copies of the network's last swapped step are done: the host then returns from a loop of
+        such steps at the pace of the link.  All other steps return as soon as they are enqueued.
         With keep_acts=True (swap must be off) the forward activations are returned too.
         With timing=True the per-call GPU durations (seconds) are left in self.call_seconds."""
         prog = self.program(x.shape, keep_acts)

@@ -6,22 +6,22 @@ import synth
 
 pytestmark = pytest.mark.gpu
 
-# (N, D, H, W, c1, c2, cout, dtype): spans direct and MFMA paths, several tiles, ragged tails
+# (N, D, H, W, c1, c2, cout, dtype): spans the general and the bf16 matrix kernels, several tiles, ragged tails
 FWD_CASES = [
     (1, 16, 16, 16, 4, 0, 8, "f32"),       # workload config 1
-    (2, 5, 6, 7, 3, 2, 5, "f32"),          # odd sizes, two sources, direct
+    (2, 5, 6, 7, 3, 2, 5, "f32"),          # odd sizes, two sources
     (1, 9, 10, 11, 1, 0, 32, "bf16"),      # single-channel first layer kernels
     (2, 6, 5, 7, 1, 0, 64, "bf16"),        # first layer, two samples (borders between samples)
     (2, 9, 11, 19, 1, 0, 128, "bf16"),     # first layer of the encoder/decoder model: 128 channels (two 64-channel wgrad passes)
-    (1, 5, 6, 7, 3, 2, 5, "bf16"),         # direct kernels in bf16
-    (1, 16, 16, 16, 32, 0, 32, "bf16"),    # MFMA, MB=1, 8 tiles
-    (1, 12, 20, 9, 32, 0, 64, "bf16"),     # MFMA, MB=2, ragged tiles
+    (1, 5, 6, 7, 3, 2, 5, "bf16"),         # general kernels in bf16
+    (1, 16, 16, 16, 32, 0, 32, "bf16"),    # small-volume kernels, from here to the plane-streaming cases: 64 tiles
+    (1, 12, 20, 9, 32, 0, 64, "bf16"),     # two output blocks, ragged tiles
     (2, 8, 8, 16, 64, 0, 32, "bf16"),      # several K chunks
     (1, 10, 8, 8, 32, 32, 32, "bf16"),     # two sources (decoder conv1)
-    (1, 4, 4, 4, 128, 0, 128, "bf16"),     # volume smaller than a tile, 2 channel groups
+    (1, 4, 4, 4, 128, 0, 128, "bf16"),     # one tile, four output blocks
     (1, 2, 2, 2, 64, 64, 64, "bf16"),      # bottleneck-like
-    (1, 7, 20, 35, 32, 0, 64, "bf16"),     # several 16x16 columns with ragged edges, odd depth
-    (2, 3, 17, 16, 64, 32, 32, "bf16"),    # two sources, one row past a column, two samples
+    (1, 7, 20, 35, 32, 0, 64, "bf16"),     # ragged edges, odd depth
+    (2, 3, 17, 16, 64, 32, 32, "bf16"),    # two sources, one row past a tile, two samples
     (1, 40, 16, 18, 32, 0, 32, "bf16"),    # long depth run
     (3, 36, 44, 50, 32, 0, 32, "bf16"),    # plane-streaming kernel (32 output channels, a tile per CU and more): ragged on every axis
     (2, 32, 40, 48, 32, 32, 96, "bf16"),   # plane-streaming forward: two sources, four chunks, three output blocks
@@ -196,13 +196,15 @@ def test_error_codes():
 
 
 BITS_CASES = [
-    (1, 16, 16, 16, 32, 0, 32),      # pipelined kernel, one output block per workgroup, 4x8x8 tiles
-    (1, 12, 20, 35, 32, 0, 64),      # ragged tiles, two blocks per workgroup
+    (1, 16, 16, 16, 32, 0, 32),      # small-volume kernel
+    (1, 12, 20, 35, 32, 0, 64),      # ragged tiles, two output blocks
+    (1, 20, 40, 44, 32, 0, 32),      # pipelined kernel, 4x8x8 tiles, one output block
+    (2, 24, 32, 39, 32, 0, 64),      # ... two blocks per workgroup forward, ragged
     (2, 9, 10, 11, 1, 0, 64),        # first layer (im2col kernel writes the bits)
     (1, 6, 7, 9, 1, 0, 48),          # first layer, thread-per-channel kernel + generic bits pass
     (1, 10, 8, 8, 32, 32, 32),       # two sources forward / two destinations backward (mask on the first)
-    (1, 4, 4, 4, 128, 0, 128),       # small volume: first MFMA kernel + generic passes
-    (1, 5, 6, 7, 3, 2, 16),          # direct kernels
+    (1, 4, 4, 4, 128, 0, 128),       # small-volume kernel
+    (1, 5, 6, 7, 3, 2, 16),          # general kernels + generic passes
     (3, 36, 44, 50, 32, 0, 32),      # plane-streaming kernel writes / reads the bits, ragged tiles, two tiles per workgroup
     (2, 32, 40, 48, 32, 64, 32),     # plane-streaming backward-data: mask on the first of two destinations
 ]
@@ -252,9 +254,11 @@ POOL_CASES = [
     (3, 36, 44, 50, 32, 0, 32, "bf16", 1),    # plane-streaming kernel pools itself: ragged tiles, two tiles per workgroup
     (2, 32, 40, 48, 32, 32, 96, "bf16", 1),   # ... two sources, three output blocks
     (3, 36, 44, 50, 32, 0, 32, "bf16", 0),    # no ReLU: the pooling kernel runs behind the convolution
-    (1, 16, 16, 16, 32, 0, 32, "bf16", 1),    # small tiles: second pass
-    (1, 12, 20, 36, 32, 0, 64, "bf16", 1),    # two blocks per workgroup: second pass
-    (1, 16, 16, 16, 4, 0, 8, "f32", 1),       # direct kernels
+    (1, 16, 16, 16, 32, 0, 32, "bf16", 1),    # small-volume kernel: second pass
+    (1, 12, 20, 36, 32, 0, 64, "bf16", 1),    # two output blocks: second pass
+    (1, 20, 40, 44, 32, 0, 32, "bf16", 1),    # 4x8x8 tiles of the pipelined kernel: second pass
+    (2, 24, 32, 40, 32, 0, 64, "bf16", 1),    # ... two blocks per workgroup: second pass
+    (1, 16, 16, 16, 4, 0, 8, "f32", 1),       # general kernels
 ]
 
 
@@ -301,7 +305,9 @@ EXACT_CASES = [
     (1, 64, 64, 64, 32, 0, 32),     # plane-streaming kernel, the benchmark's layer (K-split weight gradient)
     (1, 40, 36, 50, 64, 0, 64),     # pipelined kernel, two output blocks, ragged 8x8x16 tiles
     (2, 20, 24, 24, 32, 32, 64),    # two sources / two destinations
-    (1, 16, 16, 16, 128, 0, 128),   # 4x8x8 tiles
+    (1, 16, 16, 16, 128, 0, 128),   # small-volume kernel, four output blocks
+    (1, 13, 20, 28, 128, 0, 128),   # 4x8x8 tiles, one output block per workgroup, ragged
+    (2, 24, 32, 39, 64, 0, 64),     # 4x8x8 tiles, two blocks per workgroup
     (1, 12, 20, 9, 32, 0, 64),      # small-volume kernel
     (1, 24, 20, 36, 1, 0, 64),      # single-channel first layer
 ]

@@ -49,13 +49,13 @@ def test_static_scratch_matches_the_workspace_entry_point_twice_in_a_row(orc):
     _case(orc, 501, (1, 24, 40, 36), 64, 64, "bf16")      # pipelined kernel, two output blocks, ragged tiles
     _case(orc, 503, (1, 12, 20, 18), 32, 32, "bf16")      # K-split variant
     _case(orc, 505, (2, 10, 16, 16), 64, 32, "bf16", split=32)   # two-source input
-    _case(orc, 507, (1, 16, 16, 16), 4, 8, "f32")         # direct kernel (config-1 shape)
+    _case(orc, 507, (1, 16, 16, 16), 4, 8, "f32")         # fp32 (config-1 shape)
     _case(orc, 509, (1, 6, 6, 6), 4, 8, "f32")
 
 
 def test_shapes_beyond_the_array_are_refused():
     from paper_1811_12174_amd import k3
-    # fp32 direct kernel at 64^3, 32 -> 32: 1024 splits x 110 KB of partial sums > 64 MiB
+    # fp32 at 64^3, 32 -> 32: 1024 sets of at least 256 voxels x 110 KB of partial sums > 64 MiB
     x = torch.zeros((1, 64, 64, 64, 32), device="cuda", dtype=torch.float32)
     dy = torch.zeros_like(x)
     assert k3.conv3d_bwd_weight_workspace_bytes(x, dy) > k3.STATIC_SCRATCH_BYTES
